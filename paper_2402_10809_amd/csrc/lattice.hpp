@@ -33,10 +33,13 @@ __device__ __forceinline__ void sto(T* base, uint32_t e, T v) {
 // Remap so that each XCD works on one contiguous eighth of the compact cells:
 // the cache lines that two neighbouring waves share (x-shifted slots, rows
 // y +- 1 and z +- 1) then meet in one L2 instead of being fetched twice.  The
-// map is a permutation of [0, nb).
-__device__ __forceinline__ uint32_t xcd_block(uint32_t bid, uint32_t nb) {
-  const uint32_t q = nb >> 3, r = nb & 7u, k = bid & 7u;
-  return k * q + (k < r ? k : r) + (bid >> 3);
+// map is a permutation of [0, nb).  back: each eighth from its end to its
+// start, so that a step that follows one in the other direction begins where
+// that one's cache lines are the most recent.
+__device__ __forceinline__ uint32_t xcd_block(uint32_t bid, uint32_t nb, bool back = false) {
+  const uint32_t q = nb >> 3, r = nb & 7u, k = bid & 7u, j = bid >> 3;
+  const uint32_t n = q + (k < r ? 1u : 0u);  // blocks of XCD k
+  return k * q + (k < r ? k : r) + (back ? n - 1u - j : j);
 }
 
 // Neighbour-row pairs (cy, cz): the pull source x - c_i lies in the row
