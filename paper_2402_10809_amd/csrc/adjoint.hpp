@@ -10,9 +10,19 @@
 // collision (the paper's method section).  Its transpose is written out by hand
 // below in terms of the weighted output adjoint a_i = w_i qhat_i and its
 // moments s0 = sum a_i, s1 = sum a_i c_i, s2 = sum a_i c_i c_i, so the sweep
-// stays in registers.  The streaming transpose gathers qhat_i(x) from the
-// consumer's pulled-value adjoint at x + c_i (or the cell's own opposite slot
-// across a wall).  The porosity-jump term couples q_i(x) to phi(x + c_i); that
+// stays in registers.  The streaming transpose takes qhat_i(x) from the
+// consumer's pulled-value adjoint at x + c_i (or the cell's own opposite one
+// across a wall).  One buffer holds them in place, in the forward step's AA
+// pattern run backwards.  With a_i the adjoint of step n+1's pulled f_i:
+//   n odd:  a_i(x) sits at slot (i, x).  The reverse step of n reads qhat_i(x)
+//           from slot (i, x + c_i) ((opp i, x) across a wall) and writes its own
+//           adjoint a_i(x) to slot (opp i, x - c_i) ((i, x) across a wall);
+//   n even: qhat_i(x) is therefore at slot (opp i, x), and the reverse step
+//           writes a_i(x) to slot (i, x).
+// Within one reverse step every slot is read and written by one work-item, so
+// no two race, and after step 0 the adjoints sit at (i, x).  One buffer of 19
+// planes (179 MB on 2.36 M cells) instead of two stays in the Infinity Cache
+// from one reverse step to the next while the record streams past it.  The porosity-jump term couples q_i(x) to phi(x + c_i); that
 // contribution is gathered by the consumer cell from the producer's recorded
 // density of the previous step, so no atomics are needed.
 //
@@ -41,10 +51,10 @@ struct AdjBufs {
   const float* phi;       // porosity per compact cell
   const float* shape;     // inflow profile per row
   const double* wave;     // sampled inflow waveform
-  const float* rec;       // record of step n: [19][nc] pulled values (after the fill), [nc] omega_prev
-  const float* rho_prev;  // density of step n-1 per compact cell (null for n = 0)
-  const void* ph_next;    // adjoint of the pulled populations of step n+1, [19][nc] (FP32 or FP64)
-  void* ph_out;           // adjoint of the pulled populations of step n, [19][nc] (FP32 or FP64)
+  const float* rec;       // record of step n: [19][pl] pulled values (after the fill), [pl] omega_prev
+  const float* rho_prev;  // density of step n-1 per compact cell (read but not used at n = 0)
+  void* ph;               // adjoint of the pulled populations, [19][pl] (FP32 or FP64), in place
+  uint32_t pl;            // cells per plane of rec and ph (plane_cells)
   double* omh;            // per cell: in adjoint of omega_n, out adjoint of omega_{n-1}
   double* phih;           // per cell: porosity adjoint accumulator
   const double* aside_in; // extrapolation outflow: per row, adjoints of the 5 c_x = -1 unknowns of step n+1
@@ -53,33 +63,70 @@ struct AdjBufs {
 
 // One FP32 value per lane from a buffer straight into LDS (the wave's 64
 // consecutive slots at lds): the load occupies no register while in flight.
-__device__ __forceinline__ void gather_to_lds(__amdgpu_buffer_rsrc_t r, float* lds, uint32_t byte_off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 4, byte_off, 0, 0, 0);
+__device__ __forceinline__ void gather_to_lds(__amdgpu_buffer_rsrc_t r, float* lds, uint32_t voff, uint32_t soff = 0) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 4, voff, soff, 0, 0);
+}
+// One adjoint population to the buffer (FP32 or FP64).
+template <class PH>
+__device__ __forceinline__ void put_adjoint(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, double v) {
+  if constexpr (std::is_same<PH, double>::value) {
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, voff, soff, 0);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, (float)v), r, voff, soff, 0);
+  }
+}
+
+// The kernel's first argument (Params) read again from the kernel arguments:
+// the constants of a later phase are loaded there instead of being held in
+// scalar registers (and spilled to vector lanes) from the start.
+typedef const __attribute__((address_space(4))) Params CParams;
+__device__ __forceinline__ const CParams& params_again() {
+  uint64_t a = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return *(const CParams*)a;
 }
 
 // One reverse step at every fluid cell.  Arithmetic in FP64 (the adjoint
 // recursion has the same slow modes as the forward map, so FP32 rounding of
 // per-cell scalars would accumulate the same way); the adjoint populations are
-// stored in FP32.
+// stored in FP32 or FP64 (PH).
 //
-// Both instantiations are held to 2 waves per SIMD (at most 256 VGPRs; the
-// isotropic one needs 247, the anisotropic one 255, without scratch).
-template <bool AN, class PH = float>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
+// What bounds it: 290 B per cell (record and adjoint populations, mostly from
+// beyond the L2) next to about 1 400 VALU instructions per wave, each of which
+// alone takes about 100 us on 2.36 M cells, so the waves in flight decide how
+// far the two overlap.  With FP32 populations the kernel is held to 168 VGPRs
+// for 3 waves per SIMD: 141 us per reverse step at 2.36 M cells (512x320x320
+// vessel; 133 us even, 150 us odd), against 169 us at 2 waves and 182 us when
+// it also held the neighbours' adjoints in registers and had two population
+// buffers.  What keeps the registers down:
+//   - the gathers go straight to LDS and are read there where they are used,
+//     qhat twice; so do the per-cell accumulators (omega and porosity adjoints);
+//   - positions, the tests of the link word and the constants are made again in
+//     the later phases (opaque lk, params_again) instead of being held;
+//   - at odd n, 11 of the record's values wait in LDS during the forward
+//     recompute (53 248 B per workgroup: three workgroups fit the 160 KiB).
+// FP64 populations need 60 KB of LDS, so two workgroups per CU, and get the
+// registers of 2 waves per SIMD.
+template <bool AN, class PH, bool ODD>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(std::is_same<PH, double>::value ? 2 : 3)))
 void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   using R = double;
   constexpr bool P64 = std::is_same<PH, double>::value;  // FP64 adjoint populations
-  // The neighbour gathers (adjoint populations of step n+1, porosities and,
-  // for the porosity-jump term, densities of step n-1 at x + c_I) go straight
-  // to LDS at the start, so that their latency overlaps the forward recompute
-  // at two waves per SIMD without holding registers.  Each wave reads back
-  // only the slots its own loads wrote: no barrier, one wait for the loads.
-  __shared__ float sq[Q][BLOCK], sp[Q][BLOCK], sr[Q][BLOCK];
+  // The neighbour gathers (adjoint populations of step n+1 and, for the
+  // porosity-jump term, densities of step n-1 at x + c_I) go straight to LDS at
+  // the start, so that their latency overlaps the forward recompute without
+  // holding registers.  Each wave reads back only the slots its own loads
+  // wrote: no barrier, one wait for the loads.
+  __shared__ float sq[Q][BLOCK], sr[Q - 1][BLOCK], sh[4][BLOCK];
+  // the last pulled values of the record, across the forward recompute (see above)
+  constexpr int SDN = ODD && !P64 ? 11 : 0;
+  __shared__ float sd[SDN > 0 ? SDN : 1][BLOCK];
   // FP64 adjoint populations: their high words (the low words go to sq)
   __shared__ float sqh[P64 ? Q : 1][BLOCK];
-  const uint32_t c = xcd_block(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
+  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD) * BLOCK + threadIdx.x;
   if (c >= (uint32_t)p.nc) return;
-  const uint32_t lk = a.links[c];
+  uint32_t lk = a.links[c];
   if (lk & LK_DEAD) return;
   Pos q = position(p, c, a.code[c]);
   load_deltas(a.delta, q);
@@ -88,37 +135,41 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   const uint32_t tid = threadIdx.x, wb = tid & ~63u;  // this lane, and its wave's first slot
   // Then the record: the forward recompute waits for these loads only, while
   // the gathers issued after them are still in flight.  The per-cell adjoints
-  // read-modified-written at the end are fetched here too, so that neither
+  // read-modified-written at the end are gathered here too, so that neither
   // read stalls the wave later (a wait there would also wait for the stores).
   // Loads complete in issue order for the wait counter, so the row's deltas,
   // which the gather addresses need, are kept ahead of all of these.
   asm volatile("" ::: "memory");
   float d[Q];
 #pragma unroll
-  for (int i = 0; i < Q; ++i) d[i] = __builtin_nontemporal_load(&a.rec[(size_t)i * p.nc + c]);
-  const float omp = __builtin_nontemporal_load(&a.rec[(size_t)Q * p.nc + c]);
-  const double omh_in = a.omh[c], phih_in = a.phih[c];
+  for (int i = 0; i < Q; ++i) d[i] = __builtin_nontemporal_load(&a.rec[(size_t)i * a.pl + c]);
+  const float omp = __builtin_nontemporal_load(&a.rec[(size_t)Q * a.pl + c]);
+  constexpr uint32_t PB = sizeof(PH);  // bytes per adjoint population
+  const uint32_t plb = a.pl * PB;      // bytes per plane of adjoint populations
+  const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(a.ph, (short)0, (int)(plb * (uint32_t)Q), 0x00020000);
   {
-    const uint32_t nb = (uint32_t)p.nc * 4u;
-    constexpr uint32_t PB = sizeof(PH);  // bytes per adjoint population
-    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.ph_next), (short)0,
-                                                                        (int)((uint32_t)p.nc * PB * (uint32_t)Q),
-                                                                        0x00020000);
-    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.phi), (short)0,
-                                                                        (int)nb, 0x00020000);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.rho_prev), (short)0,
-                                                                        (int)nb, 0x00020000);
+                                                                        (int)((uint32_t)p.nc * 4u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc(a.phih, (short)0, (int)((uint32_t)p.nc * 8u),
+                                                                        0x00020000);
+    gather_to_lds(rh, &sh[0][wb], c * 8u);
+    gather_to_lds(rh, &sh[1][wb], c * 8u + 4u);
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(a.omh, (short)0, (int)((uint32_t)p.nc * 8u),
+                                                                        0x00020000);
+    gather_to_lds(ro, &sh[2][wb], c * 8u);
+    gather_to_lds(ro, &sh[3][wb], c * 8u + 4u);
     gather_to_lds(rq, &sq[0][wb], c * PB);
     if constexpr (P64) gather_to_lds(rq, &sqh[0][wb], c * PB + 4u);
     sfor<1, Q>([&](auto ic) {
       constexpr int I = decltype(ic)::value;
       const bool fl = ((lk >> OPP[I]) & 1u) == 0;  // x + c_I is a fluid cell
       const uint32_t tgt = fl ? src_of<OPP[I]>(p, q) : c;  // x + c_I (the cell itself across a wall)
-      const uint32_t e = fl ? (uint32_t)I * (uint32_t)p.nc + tgt : (uint32_t)OPP[I] * (uint32_t)p.nc + c;
-      gather_to_lds(rq, &sq[I][wb], e * PB);
-      if constexpr (P64) gather_to_lds(rq, &sqh[I][wb], e * PB + 4u);
-      gather_to_lds(rp, &sp[I][wb], tgt * 4u);
-      if (a.rho_prev) gather_to_lds(rr, &sr[I][wb], tgt * 4u);
+      // the slot of qhat_I at this parity (see the layout above)
+      const uint32_t vo = ODD ? (fl ? (uint32_t)I * plb + tgt * PB : (uint32_t)OPP[I] * plb + c * PB) : c * PB;
+      const uint32_t so = ODD ? 0u : (uint32_t)OPP[I] * plb;
+      gather_to_lds(rq, &sq[I][wb], vo, so);
+      if constexpr (P64) gather_to_lds(rq, &sqh[I][wb], vo + 4u, so);
+      gather_to_lds(rr, &sr[I - 1][wb], tgt * 4u);
     });
   }
 
@@ -127,12 +178,14 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   // their transposes below (the extrapolation's unknowns are inputs)
   const bool extrap = p.outlet == 2;
   if (!(extrap && (lk & LK_OUT))) open_fill(p, q.row, lk, t, a.shape, a.wave, nullptr, d);
+  const Sums<R> sm = moment_sums<R>(d);
   Macro<R> M;
-  macro<R, AN>(p, phx_f, d, omp, M);
+#pragma unroll
+  for (int i = 0; i < SDN; ++i) sd[i][tid] = d[Q - SDN + i];
+  macro_sums<R, AN>(p, phx_f, sm, omp, M);
   const R phx = (R)phx_f;
   const R iphi = fast_rcp(phx);
-  const Sums<R> sm = moment_sums<R>(d);
-  const auto& kc = p.d;
+  const auto& kc = params_again().d;
   const R iU = kc.iU;
   const R S = phx + sm.s * iU;  // sum f = phi rho
   const R mx = sm.mx * iU, my = sm.my * iU, mz = sm.mz * iU;
@@ -143,7 +196,7 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   const R D = phx * dark;                       // phi^2 nu / k
   const R rho = M.rho, ux = M.ux, uy = M.uy, uz = M.uz, uu = M.uu;
   const R Fx = M.Fx, Fy = M.Fy, Fz = M.Fz;
-  const R om = M.omega;
+  const R om = M.omega, irho = fast_rcp(rho);
   const R Nn = M.pnorm;  // |Pi|_F
   // Carreau-Yasuda viscosity and its derivative in the shear rate, in FP64
   // like the forward passes of the adjoint
@@ -167,39 +220,59 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
       return sq[i][tid];
     }
   };
-  PH qh[Q];
-  qh[0] = rdq(0);
-  uint32_t fmask = 0;
-  R sfl = 0.0, sjump = 0.0;
-  sfor<1, Q>([&](auto ic) {
-    constexpr int I = decltype(ic)::value;
-    const bool fl = ((lk >> OPP[I]) & 1u) == 0;  // x + c_I is a fluid cell
-    const R pn = (R)sp[I][tid];
-    qh[I] = rdq(I);
-    const R ai = (R)kw(I) * (1.0 / 36.0) * (R)qh[I];
-    sfl += fl ? ai : 0.0;
-    sjump += fl ? ai * (pn - phx) : 0.0;
-    fmask |= fl ? (1u << I) : 0u;
+  // (opaque here and below, so that the tests of its bits are made where they
+  // are used instead of being held as 18 lane masks from the gathers on)
+  asm volatile("" : "+v"(lk));
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < SDN; ++i) d[Q - SDN + i] = sd[i][tid];
+  // moments of a_i = w_i qhat_i over the opposite pairs, in units of 1/36 (36 w_i
+  // is 2 on the axis pairs, 1 on the edges), and their sum over the fluid neighbours
+  R s0 = 12.0 * (R)rdq(0), s1x = 0.0, s1y = 0.0, s1z = 0.0, s2[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  R sfl = 0.0, qd = (R)rdq(0) * (R)d[0], qd2 = 0.0;
+  sfor<0, (Q - 1) / 2>([&](auto kc_) {
+    constexpr int I = 1 + 2 * decltype(kc_)::value, J = I + 1;
+    const PH qi = rdq(I), qj = rdq(J);
+    const bool fi = ((lk >> J) & 1u) == 0, fj = ((lk >> I) & 1u) == 0;  // x + c_I, x + c_J is a fluid cell
+    const R ai = I < 7 ? (R)qi + (R)qi : (R)qi, aj = I < 7 ? (R)qj + (R)qj : (R)qj;
+    qd = fma((R)qi, (R)d[I], qd);
+    qd2 = fma((R)qj, (R)d[J], qd2);
+    const R P = ai + aj, Mi = ai - aj;
+    s0 += P;
+    if constexpr (CX[I] != 0) { s1x += CX[I] > 0 ? Mi : -Mi; s2[0] += P; }
+    if constexpr (CY[I] != 0) { s1y += CY[I] > 0 ? Mi : -Mi; s2[1] += P; }
+    if constexpr (CZ[I] != 0) { s1z += CZ[I] > 0 ? Mi : -Mi; s2[2] += P; }
+    if constexpr (CX[I] * CY[I] != 0) s2[3] += CX[I] * CY[I] > 0 ? P : -P;
+    if constexpr (CX[I] * CZ[I] != 0) s2[4] += CX[I] * CZ[I] > 0 ? P : -P;
+    if constexpr (CY[I] * CZ[I] != 0) s2[5] += CY[I] * CZ[I] > 0 ? P : -P;
+    const R z = (R)0;
+    sfl += fi ? ai : z;
+    sfl += fj ? aj : z;
   });
-
-  // moments of a_i = w_i qhat_i (exact weights 36 w_i / 36)
-  R av[Q];
+  // the porosity-jump sum over the fluid neighbours; in a wave of uniform
+  // porosity every term is zero (across a wall the cell's own porosity stands
+  // for the neighbour's: an exact zero too)
+  R sjump = 0.0;
+  if (!__all((lk & LK_UNI) != 0u)) {
+    asm volatile("" ::: "memory");
+    q = position(p, c, a.code[c]);
+    load_deltas(a.delta, q);
+    float pn[Q];
+    sfor<1, Q>([&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      pn[I] = ldo(a.phi, ((lk >> OPP[I]) & 1u) == 0 ? src_of<OPP[I]>(p, q) : c);
+    });
+    sfor<1, Q>([&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      const R ai = I < 7 ? (R)rdq(I) + (R)rdq(I) : (R)rdq(I);
+      sjump = fma(ai, (R)pn[I] - phx, sjump);
+    });
+  }
+  constexpr R W36 = 1.0 / 36.0;
+  s0 *= W36; s1x *= W36; s1y *= W36; s1z *= W36; sfl *= W36; sjump *= W36;
 #pragma unroll
-  for (int i = 0; i < Q; ++i) av[i] = (R)kw(i) * (R)qh[i] * (1.0 / 36.0);
-  R s0 = 0.0, qd = 0.0;
-#pragma unroll
-  for (int i = 0; i < Q; ++i) { s0 += av[i]; qd += (R)qh[i] * (R)d[i]; }
-  qd *= iU;  // sum qhat_i (f_i - w_i phi)
-  const R s1x = (av[1] + av[7] + av[9] + av[11] + av[13]) - (av[2] + av[8] + av[10] + av[12] + av[14]);
-  const R s1y = (av[3] + av[7] + av[10] + av[15] + av[17]) - (av[4] + av[8] + av[9] + av[16] + av[18]);
-  const R s1z = (av[5] + av[11] + av[14] + av[15] + av[18]) - (av[6] + av[12] + av[13] + av[16] + av[17]);
-  R s2[6];
-  s2[0] = av[1] + av[2] + av[7] + av[8] + av[9] + av[10] + av[11] + av[12] + av[13] + av[14];
-  s2[1] = av[3] + av[4] + av[7] + av[8] + av[9] + av[10] + av[15] + av[16] + av[17] + av[18];
-  s2[2] = av[5] + av[6] + av[11] + av[12] + av[13] + av[14] + av[15] + av[16] + av[17] + av[18];
-  s2[3] = (av[7] + av[8]) - (av[9] + av[10]);
-  s2[4] = (av[11] + av[12]) - (av[13] + av[14]);
-  s2[5] = (av[15] + av[16]) - (av[17] + av[18]);
+  for (int k = 0; k < 6; ++k) s2[k] *= W36;
+  qd = (qd + qd2) * iU;  // sum qhat_i (f_i - w_i phi)
 
   const R pr = phx * rho;
   const R K = 1.0 - 0.5 * om, keep = 1.0 - om;
@@ -240,7 +313,8 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   }
 
   // collision: q = (1-omega) f + omega feq + K g + w rho (phi~ - phi)
-  R omh = omh_in + wom + (Aeq * s0 + 3.0 * pr * s1u + 4.5 * pr * us2u - qd) -
+  const uint64_t om_lo = __builtin_bit_cast(uint32_t, sh[2][tid]), om_hi = __builtin_bit_cast(uint32_t, sh[3][tid]);
+  R omh = __builtin_bit_cast(double, om_lo | (om_hi << 32)) + wom + (Aeq * s0 + 3.0 * pr * s1u + 4.5 * pr * us2u - qd) -
           0.5 * (3.0 * s1F - 3.0 * s0 * uF + 9.0 * us2F);
   R uhx = K * (9.0 * s2Fx - 3.0 * s0 * Fx), uhy = K * (9.0 * s2Fy - 3.0 * s0 * Fy),
     uhz = K * (9.0 * s2Fz - 3.0 * s0 * Fz);
@@ -256,12 +330,11 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   R phh = rho * brk - rho * sfl;
 
   // relaxation rate omega = 2 rho / (6 nu + rho), nu = CY(shear)
-  const R den6 = 6.0 * nu + rho;
-  const R id2 = fast_rcp(den6 * den6);
+  const R rden = 0.5 * om * irho;  // 1 / (6 nu + rho)
+  const R id2 = rden * rden;
   rhoh += omh * 12.0 * nu * id2;
   const R nuh = -omh * 12.0 * rho * id2;
   const R gh = nuh * dnu;
-  const R irho = fast_rcp(rho);
   const R omph = gh * 3.0 * Nn * irho;      // adjoint of omega_prev
   const R Nh = gh * 3.0 * (R)omp * irho;
   rhoh -= gh * shear * irho;
@@ -296,14 +369,17 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   const R ddark = -2.0 * kn * om1 * iphi * iphi * iphi;    // d(phi nu / k)/dphi
   rhoh += (Fhx * Fx + Fhy * Fy + Fhz * Fz) * irho;
   R vhx, vhy, vhz;
-  const R iS = fast_rcp(S);
+  const R iS = iphi * irho;
   const R vx = mx * iS + 0.5 * kc.gx * iphi, vy = my * iS + 0.5 * kc.gy * iphi, vz = mz * iS + 0.5 * kc.gz * iphi;
   if constexpr (AN) {
+    R Mi[6], Mh[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) { Mi[k] = kc.Mi[k]; Mh[k] = kc.Mh[k]; }
     R kdx, kdy, kdz, khx, khy, khz, mfx, mfy, mfz, hfx, hfy, hfz;
-    sym_mv(kc.Mi, ux, uy, uz, kdx, kdy, kdz);
-    sym_mv(kc.Mh, ux, uy, uz, khx, khy, khz);
-    sym_mv(kc.Mi, Fhx, Fhy, Fhz, mfx, mfy, mfz);
-    sym_mv(kc.Mh, Fhx, Fhy, Fhz, hfx, hfy, hfz);
+    sym_mv(Mi, ux, uy, uz, kdx, kdy, kdz);
+    sym_mv(Mh, ux, uy, uz, khx, khy, khz);
+    sym_mv(Mi, Fhx, Fhy, Fhz, mfx, mfy, mfz);
+    sym_mv(Mh, Fhx, Fhy, Fhz, hfx, hfy, hfz);
     uhx -= rho * (D * mfx + E * un * hfx);
     uhy -= rho * (D * mfy + E * un * hfy);
     uhz -= rho * (D * mfz + E * un * hfz);
@@ -408,15 +484,26 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   Sh += rhoh * iphi;
   phh -= rhoh * rho * iphi;
 
-  // adjoint of the (filled) pulled populations
+  // adjoint of the (filled) pulled populations; the odd part flips sign within
+  // an opposite pair.  qhat is read from LDS again rather than held across the
+  // sweep, and the position (for the stores) and the open-face rows likewise.
+  asm volatile("" : "+v"(lk) : : "memory");
+  q = position(p, c, a.code[c]);
+  if (ODD) load_deltas(a.delta, q);
   R fh[Q];
-  fh[0] = keep * (R)qh[0] + Sh;
-  sfor<1, Q>([&](auto ic) {
-    constexpr int I = decltype(ic)::value;
+  fh[0] = fma(keep, (R)rdq(0), Sh);
+  sfor<0, (Q - 1) / 2>([&](auto kc_) {
+    constexpr int I = 1 + 2 * decltype(kc_)::value, J = I + 1;
     constexpr int cx = CX[I], cy = CY[I], cz = CZ[I];
-    fh[I] = keep * (R)qh[I] + Sh + mhx * (R)cx + mhy * (R)cy + mhz * (R)cz + (R)(cx * cx) * G[0] +
-            (R)(cy * cy) * G[1] + (R)(cz * cz) * G[2] +
-            2.0 * ((R)(cx * cy) * G[3] + (R)(cx * cz) * G[4] + (R)(cy * cz) * G[5]);
+    R ev = Sh, od = 0.0;
+    if constexpr (cx != 0) { ev += G[0]; od += cx > 0 ? mhx : -mhx; }
+    if constexpr (cy != 0) { ev += G[1]; od += cy > 0 ? mhy : -mhy; }
+    if constexpr (cz != 0) { ev += G[2]; od += cz > 0 ? mhz : -mhz; }
+    if constexpr (cx * cy != 0) ev = fma(2.0 * (cx * cy), G[3], ev);
+    if constexpr (cx * cz != 0) ev = fma(2.0 * (cx * cz), G[4], ev);
+    if constexpr (cy * cz != 0) ev = fma(2.0 * (cy * cz), G[5], ev);
+    fh[I] = fma(keep, (R)rdq(I), ev + od);
+    fh[J] = fma(keep, (R)rdq(J), ev - od);
   });
 
   // the -x neighbour of an extrapolation-outflow cell: its c_x = -1 pulled
@@ -466,22 +553,34 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
     fh[5] += nzh; fh[6] -= nzh; fh[15] += nzh; fh[16] -= nzh; fh[17] -= nzh; fh[18] += nzh;
     fh[2] = 0.0; fh[8] = 0.0; fh[10] = 0.0; fh[12] = 0.0; fh[14] = 0.0;
   }
-#pragma unroll
-  for (int i = 0; i < Q; ++i) sto((PH*)a.ph_out, (uint32_t)i * (uint32_t)p.nc + c, (PH)fh[i]);
+  // into the slots just read: at odd n to where the producer x - c_i finds it
+  // among its own (the cell's own slot across a wall), at even n to (i, x)
+  sfor<0, Q>([&](auto ic) {
+    constexpr int I = decltype(ic)::value;
+    const bool push = ODD && I > 0 && ((lk >> I) & 1u) == 0;  // x - c_I is a fluid cell
+    if constexpr (ODD && I > 0)
+      put_adjoint<PH>(rq, push ? (uint32_t)OPP[I] * plb + src_of<I>(p, q) * PB : (uint32_t)I * plb + c * PB, 0u, fh[I]);
+    else
+      put_adjoint<PH>(rq, c * PB, (uint32_t)I * plb, fh[I]);
+  });
   a.omh[c] = omph;
 
   // porosity-jump term of step n-1: q_i(x - c_i) depends on phi(x) when
   // x - c_i is a fluid producer; its adjoint is w_i rho_{n-1}(x - c_i) fh_i(x).
-  if (a.rho_prev) {
+  if (t > 0u) {
+    R jump_a = 0.0, jump_e = 0.0;
     sfor<1, Q>([&](auto ic) {
       constexpr int J = decltype(ic)::value;
-      // rho_{n-1}(x + c_J), staged in LDS; every slot is read and the sum
-      // selected, so that the LDS reads are not serialised behind branches
-      const R t = fma((R)kw(J) * (1.0 / 36.0) * (R)sr[J][tid], fh[OPP[J]], phh);
-      phh = (fmask & (1u << J)) ? t : phh;
+      // rho_{n-1}(x + c_J), staged in LDS; every slot is read and selected, so
+      // that the LDS reads are not serialised behind branches
+      const float r = ((lk >> OPP[J]) & 1u) == 0 ? sr[J - 1][tid] : 0.0f;
+      if constexpr (J < 7) jump_a = fma((R)r, fh[OPP[J]], jump_a);
+      else jump_e = fma((R)r, fh[OPP[J]], jump_e);
     });
+    phh += W36 * fma(2.0, jump_a, jump_e);
   }
-  a.phih[c] = phih_in + phh;
+  const uint64_t ph_lo = __builtin_bit_cast(uint32_t, sh[0][tid]), ph_hi = __builtin_bit_cast(uint32_t, sh[1][tid]);
+  a.phih[c] = __builtin_bit_cast(double, ph_lo | (ph_hi << 32)) + phh;
 }
 
 // Rest state f_i(0, x) = w_i phi(x) on the known links (and on the
@@ -489,7 +588,7 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
 // then scatter the total into the box-layout gradient.
 template <class PH>
 __global__ __launch_bounds__(BLOCK) void k_adj_final(Params p, const uint32_t* code, const uint32_t* links,
-                                                     const uint32_t* rowbox, const PH* ph0, const double* total,
+                                                     const uint32_t* rowbox, const PH* ph0, uint32_t pl, const double* total,
                                                      const double* aside0, float* grad) {
   const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
   if (c >= (uint32_t)p.nc) return;
@@ -498,7 +597,7 @@ __global__ __launch_bounds__(BLOCK) void k_adj_final(Params p, const uint32_t* c
   const Pos q = position(p, c, code[c]);
   double s = total[c];
 #pragma unroll
-  for (int i = 0; i < Q; ++i) s += (double)kw(i) * (1.0 / 36.0) * (double)ldo(ph0, (uint32_t)i * (uint32_t)p.nc + c);
+  for (int i = 0; i < Q; ++i) s += (double)kw(i) * (1.0 / 36.0) * (double)ldo(ph0, (uint32_t)i * pl + c);
   if (p.outlet == 2 && (lk & LK_OUT)) {
 #pragma unroll
     for (int k = 0; k < 5; ++k) s += (double)kw(XOUT[k]) * (1.0 / 36.0) * aside0[(size_t)q.row * 5 + k];

@@ -48,7 +48,7 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
     ~ArithScope() { c->amode = saved; }
   } arith_scope{c, c->amode};
   c->amode = 2;
-  const size_t nc = (size_t)c->nc, nbox = c->nbox;
+  const size_t nc = (size_t)c->nc, pl = (size_t)plane_cells(c->nc), nbox = c->nbox;
   const int nseg = (T + ckpt - 1) / ckpt;
   float* ck = (float*)(c->ws + L.ck);
   float* rec = (float*)(c->ws + L.rec);
@@ -56,7 +56,7 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
   double* omh = (double*)(c->ws + L.omh);
   double* phih = (double*)(c->ws + L.phih);
   double* objp = (double*)(c->ws + L.obj);
-  auto slot_rec = [&](int k) { return rec + (size_t)k * (Q + 1) * nc; };
+  auto slot_rec = [&](int k) { return rec + (size_t)k * (Q + 1) * pl; };
   auto slot_rho = [&](int k) { return rho + (size_t)k * nc; };
   // checkpoint s: the state at time s * ckpt - 1 (c->t at the call)
   auto save_ck = [&](int s) -> lbm_status {
@@ -112,14 +112,12 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
   }
 
   // reverse sweep
-  // adjoint of the pulled populations of steps n+1 and n, FP32 or FP64 (the
+  // adjoint of the pulled populations, in place, FP32 or FP64 (the
   // workspace holds room for FP64)
   const bool p64 = obj->fp64_adjoint != 0;
   const size_t pb = p64 ? 8 : 4;
-  void* phn = (void*)(c->ws + L.ah0);
-  void* pho = (void*)(c->ws + L.ah1);
-  HIP_TRY(c, hipMemsetAsync(phn, 0, Q * nc * pb, c->stream));
-  HIP_TRY(c, hipMemsetAsync(pho, 0, Q * nc * pb, c->stream));
+  void* ph = (void*)(c->ws + L.ah);
+  HIP_TRY(c, hipMemsetAsync(ph, 0, Q * pl * pb, c->stream));
   HIP_TRY(c, hipMemsetAsync(omh, 0, nc * 8, c->stream));
   HIP_TRY(c, hipMemsetAsync(phih, 0, nc * 8, c->stream));
   // extrapolation outflow: adjoints of the kept unknowns, per row, by parity
@@ -135,6 +133,8 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
   ab.wave = (const double*)(c->ws + c->L.wave);
   ab.omh = omh;
   ab.phih = phih;
+  ab.ph = ph;
+  ab.pl = (uint32_t)pl;
   for (int s = nseg - 1; s >= 0; --s) {
     const int t0 = s * ckpt, t1 = std::min(T, t0 + ckpt);
     if (s < s_last) {
@@ -155,36 +155,31 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
     for (int n = t1 - 1; n >= t0; --n) {
       const int k = n - t0 + 1;
       ab.rec = slot_rec(k);
-      ab.rho_prev = n > 0 ? slot_rho(k - 1) : nullptr;
-      ab.ph_next = phn;
-      ab.ph_out = pho;
+      ab.rho_prev = slot_rho(k - 1);
       ab.aside_in = aside + (size_t)((n + 1) & 1) * c->nrow * 5;
       ab.aside_out = aside + (size_t)(n & 1) * c->nrow * 5;
       const float ewn = (n >= obj->t_begin && n < obj->t_end) ? (float)ew : 0.0f;
-      if (c->P.an_iters > 0 && p64)
-        hipLaunchKernelGGL((k_adjoint<true, double>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab, (uint32_t)n,
-                           ewn, okind);
-      else if (c->P.an_iters > 0)
-        hipLaunchKernelGGL((k_adjoint<true, float>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab, (uint32_t)n,
-                           ewn, okind);
-      else if (p64)
-        hipLaunchKernelGGL((k_adjoint<false, double>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab,
-                           (uint32_t)n, ewn, okind);
-      else
-        hipLaunchKernelGGL((k_adjoint<false, float>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab,
-                           (uint32_t)n, ewn, okind);
+      auto reverse = [&](auto an, auto ph_type, auto odd) {
+        hipLaunchKernelGGL((k_adjoint<decltype(an)::value, decltype(ph_type), decltype(odd)::value>), dim3(c->nblk),
+                           dim3(BLOCK), 0, c->stream, c->P, ab, (uint32_t)n, ewn, okind);
+      };
+      with_parity(n, [&](auto odd) {
+        if (c->P.an_iters > 0 && p64) reverse(std::true_type{}, double{}, odd);
+        else if (c->P.an_iters > 0) reverse(std::true_type{}, float{}, odd);
+        else if (p64) reverse(std::false_type{}, double{}, odd);
+        else reverse(std::false_type{}, float{}, odd);
+      });
       HIP_TRY(c, hipGetLastError());
-      std::swap(phn, pho);
     }
   }
   HIP_TRY(c, hipMemsetAsync(dJ_dphi, 0, nbox * 4, c->stream));
   if (p64)
     hipLaunchKernelGGL(k_adj_final<double>, dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab.code, ab.links,
-                       (const uint32_t*)(c->ws + c->L.rowbox), (const double*)phn, (const double*)phih,
+                       (const uint32_t*)(c->ws + c->L.rowbox), (const double*)ph, (uint32_t)pl, (const double*)phih,
                        (const double*)aside, dJ_dphi);
   else
     hipLaunchKernelGGL(k_adj_final<float>, dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab.code, ab.links,
-                       (const uint32_t*)(c->ws + c->L.rowbox), (const float*)phn, (const double*)phih,
+                       (const uint32_t*)(c->ws + c->L.rowbox), (const float*)ph, (uint32_t)pl, (const double*)phih,
                        (const double*)aside, dJ_dphi);
   HIP_TRY(c, hipGetLastError());
   // leave the context at the rest state

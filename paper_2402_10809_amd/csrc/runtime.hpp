@@ -41,7 +41,7 @@ inline int step_nt(int storage) { return storage == LBM_STORE_FP32 ? 256 : STEP_
 struct Layout {
   size_t A, code, links, phi, omega, delta, rel, winfo, shape, rowbox, stage, part, diag, obj, tc, wave, side;
   // adjoint
-  size_t ck, rec, rho, ah0, ah1, omh, phih, aside;
+  size_t ck, rec, rho, ah, omh, phih, aside;
   int nck, ckpt, T;
   size_t total;
 };

@@ -133,7 +133,7 @@ struct Bufs {
   const float* shape;     // inflow profile per row
   const uint32_t* rowbox; // box index of (x = 0) of each row
   double* part;           // per-block partials
-  float* rec;             // recompute record: [20][nc] (pulled values, omega_prev)
+  float* rec;             // recompute record: [20][plane cells] (pulled values, omega_prev)
   float* rho_rec;         // recompute record: rho per compact cell
   uint32_t* tc;           // time counter: the step at parity k reads tc[k] and writes t + 1 to tc[1 - k]
   const double* wave;     // sampled inflow waveform (in_table entries)
@@ -992,6 +992,10 @@ __device__ __forceinline__ void diag_terms(const Params& p, float phx, const flo
   v[10] = (double)region_wss<R>(lk, M);
 }
 
+// Cells per plane of a step's record: that of the FP32 population planes, so
+// that a wave's record accesses cover whole cache lines too.
+__device__ __forceinline__ uint32_t rec_plane(const Params& p) { return p.plb[1] >> 2; }
+
 // Body of the step for one cell (UNI: the whole wave has uniform neighbour
 // porosity; INR: every cell of the wave is interior; RM: rounding of 16-bit
 // storage, see round16).
@@ -1029,7 +1033,7 @@ __device__ __forceinline__ void step_cell(const Params& p, const Bufs& b, uint32
     // extrapolation outflow's unknowns) is read once, by the reverse step:
     // stream it past the caches
 #pragma unroll
-    for (int i = 0; i < Q; ++i) __builtin_nontemporal_store(d[i], &b.rec[(size_t)i * p.nc + c]);
+    for (int i = 0; i < Q; ++i) __builtin_nontemporal_store(d[i], &b.rec[(size_t)i * rec_plane(p) + c]);
   }
   if (p.outlet == 2 && (lk & (LK_OUT | LK_UPS))) outflow_keep(p, q.row, lk, phx, d, b.side + (ODD ? 0 : half));
   const float omp = b.omega[c];
@@ -1037,7 +1041,7 @@ __device__ __forceinline__ void step_cell(const Params& p, const Bufs& b, uint32
   macro<R, AN, PF>(p, phx, d, omp, M);
   b.omega[c] = (float)M.omega;
   if (REC) {
-    __builtin_nontemporal_store(omp, &b.rec[(size_t)Q * p.nc + c]);
+    __builtin_nontemporal_store(omp, &b.rec[(size_t)Q * rec_plane(p) + c]);
     __builtin_nontemporal_store((float)M.rho, &b.rho_rec[c]);
   }
   const bool reg = (lk & LK_REG) != 0;
