@@ -1,8 +1,14 @@
 """The reverse sweep's in-place adjoint populations against the FP64 oracle: first
 reverse steps of both parities (T odd and even, down to one step), every
-segment length around them, FP32 and FP64 populations.  Bound: the gradient
-tolerance of the adjoint, 1e-4 of the largest entry (FP32 populations: 19
-roundings of 2^-24 a step, below 1e-5 over five steps).
+segment length around them, FP32 and FP64 populations.
+
+Bound on an entry's error: the gradient tolerance of the adjoint, 1e-4 of the
+largest entry, plus what FP32 storage leaves of an entry that cancels to zero.
+After one step the gradient does vanish (the oracle holds 1e-20 of it), so only
+the second term bounds it there: an entry is sum_i w_i a_i over the stored
+adjoints a_i, each rounded to 2^-24 of itself a step, and with the region mean
+of rho |u|^2 / 2 as objective |a_i| is at most |c_i| |u| / N + |u|^2 / 2N <= 2 |u| / N
+on a region of N cells, |u| <= sqrt(2 J N).
 """
 
 import numpy as np
@@ -29,8 +35,10 @@ def test_short_reverse_sweeps(kind, T, ckpt, fp64):
     s = Solver.from_case(case, adjoint_T=T, ckpt=ckpt)
     J, g = s.adjoint(0, T, T, ckpt, kind="ke", fp64=fp64)
     fluid = case.solid == 0
+    region = int((case.sac & fluid).sum())
     scale = np.abs(g_ref)[fluid].max()
-    err = np.abs(g.cpu().numpy() - g_ref)[fluid].max() / max(scale, 1e-300)
-    print(f"  J {J:.10e} oracle {J_ref:.10e}; gradient max-rel {err:.3e} of {scale:.3e}", flush=True)
+    err = np.abs(g.cpu().numpy() - g_ref)[fluid].max()
+    stored = T * 2.0 ** -24 * 2.0 * np.sqrt(2.0 * J_ref / region)
+    print(f"  J {J:.10e} oracle {J_ref:.10e}; gradient error {err:.3e} of {scale:.3e}, storage {stored:.3e}", flush=True)
     assert abs(J - J_ref) <= 1e-5 * abs(J_ref) + 1e-30
-    assert err < 1e-4 or scale < 1e-20
+    assert err < 1e-4 * scale + stored
