@@ -34,7 +34,7 @@
 // them to the -x neighbour's pulled values.
 //
 // AN: the anisotropic permeability of the method section's Remark, whose
-// fixed-point iterates are recomputed from v inside the reverse step.
+// fixed-point iterates the reverse step goes back through.
 //
 // Supported: FP32 storage, shift mode 0, with or without Forchheimer drag,
 // isotropic or anisotropic permeability, D3Q19.  The recompute uses the same
@@ -106,10 +106,10 @@ __device__ __forceinline__ const CParams& params_again() {
 //     the later phases (opaque lk, params_again) instead of being held;
 //   - at odd n, 11 of the record's values wait in LDS during the forward
 //     recompute (53 248 B per workgroup: three workgroups fit the 160 KiB).
-// FP64 populations need 60 KB of LDS, so two workgroups per CU, and get the
-// registers of 2 waves per SIMD.
+// FP64 populations need 60 KB of LDS and the anisotropic medium 20 KB for its
+// iterates, so two workgroups per CU, and get the registers of 2 waves per SIMD.
 template <bool AN, class PH, bool ODD>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(std::is_same<PH, double>::value ? 2 : 3)))
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(AN || std::is_same<PH, double>::value ? 2 : 3)))
 void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   using R = double;
   constexpr bool P64 = std::is_same<PH, double>::value;  // FP64 adjoint populations
@@ -120,8 +120,11 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   // wrote: no barrier, one wait for the loads.
   __shared__ float sq[Q][BLOCK], sr[Q - 1][BLOCK], sh[4][BLOCK];
   // the last pulled values of the record, across the forward recompute (see above)
-  constexpr int SDN = ODD && !P64 ? 11 : 0;
+  constexpr int SDN = ODD && !P64 && !AN ? 11 : 0;
   __shared__ float sd[SDN > 0 ? SDN : 1][BLOCK];
+  // anisotropic permeability: |u_m| of the first iterates
+  constexpr int NIT = AN ? 10 : 1;
+  __shared__ double sn[NIT][BLOCK];
   // FP64 adjoint populations: their high words (the low words go to sq)
   __shared__ float sqh[P64 ? Q : 1][BLOCK];
   const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD) * BLOCK + threadIdx.x;
@@ -182,7 +185,9 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   Macro<R> M;
 #pragma unroll
   for (int i = 0; i < SDN; ++i) sd[i][tid] = d[Q - SDN + i];
-  macro_sums<R, AN>(p, phx_f, sm, omp, M);
+  macro_sums<R, AN>(p, phx_f, sm, omp, M, [&](int m, R n) {
+    if (m < NIT) sn[m][tid] = n;
+  });
   const R phx = (R)phx_f;
   const R iphi = fast_rcp(phx);
   const auto& kc = params_again().d;
@@ -390,51 +395,76 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
       phh += rho * un * Fkh * K2;
     }
     phh -= rho * Fkd * dD;
-    // the fixed-point iterates u_{m+1} = X_m^-1 v, X_m = A + |u_m| B, u_0 = v,
-    // A = Id + (phi nu / 2k) M^-1, B = C1 M^-1/2: back through the iterates,
-    // recomputing u_m from v each time
+    // the fixed-point iterates u_{m+1} = X_m^-1 v, X_m = A + n_m B, n_m = |u_m|,
+    // u_0 = v, A = Id + (phi nu / 2k) M^-1, B = C1 M^-1/2: back through the
+    // iterates.  n_m alone fixes X_m and so u_{m+1}, and the forward recompute
+    // left the first NIT of them in LDS; one adjugate of X_m serves both u_{m+1}
+    // and the adjoint (X symmetric).  (Recomputing every u_m from v instead took
+    // 27 solves for 6 iterates, now 6: 24.7 -> 20.6 us per reverse step at
+    // 118 304 cells with FP64 populations.)
     const R ha = 0.5 * dark, hb = forch ? 0.5 * K2 * om1 * iphi : 0.0;
-    // y = X^-1 b for X = A + n B (symmetric: the adjugate over the determinant).
-    // X is formed from the uniform shape matrices at each solve rather than
-    // kept per work-item, which keeps the kernel's registers down.
-    auto solve = [&](R n, R bx, R by, R bz, R& yx, R& yy, R& yz) {
+    struct Adj {
+      R a00, a11, a22, a01, a02, a12, id;
+      __device__ __forceinline__ void apply(R bx, R by, R bz, R& yx, R& yy, R& yz) const {
+        yx = (a00 * bx + a01 * by + a02 * bz) * id;
+        yy = (a01 * bx + a11 * by + a12 * bz) * id;
+        yz = (a02 * bx + a12 * by + a22 * bz) * id;
+      }
+    };
+    // X^-1 of X = A + n B (the adjugate over the determinant)
+    auto inverse = [&](R n) {
       R X[6];
       const R nb = n * hb;
 #pragma unroll
-      for (int k = 0; k < 6; ++k) X[k] = ha * kc.Mi[k] + nb * kc.Mh[k] + (k < 3 ? 1.0 : 0.0);
-      const R a00 = X[1] * X[2] - X[5] * X[5], a11 = X[0] * X[2] - X[4] * X[4], a22 = X[0] * X[1] - X[3] * X[3];
-      const R a01 = X[4] * X[5] - X[3] * X[2], a02 = X[3] * X[5] - X[4] * X[1], a12 = X[3] * X[4] - X[0] * X[5];
-      const R idet = fast_rcp(X[0] * a00 + X[3] * a01 + X[4] * a02);
-      yx = (a00 * bx + a01 * by + a02 * bz) * idet;
-      yy = (a01 * bx + a11 * by + a12 * bz) * idet;
-      yz = (a02 * bx + a12 * by + a22 * bz) * idet;
+      for (int k = 0; k < 6; ++k) X[k] = ha * Mi[k] + nb * Mh[k] + (k < 3 ? 1.0 : 0.0);
+      Adj r;
+      r.a00 = X[1] * X[2] - X[5] * X[5]; r.a11 = X[0] * X[2] - X[4] * X[4]; r.a22 = X[0] * X[1] - X[3] * X[3];
+      r.a01 = X[4] * X[5] - X[3] * X[2]; r.a02 = X[3] * X[5] - X[4] * X[1]; r.a12 = X[3] * X[4] - X[0] * X[5];
+      r.id = fast_rcp(X[0] * r.a00 + X[3] * r.a01 + X[4] * r.a02);
+      return r;
     };
-    R ubx = uhx, uby = uhy, ubz = uhz;  // adjoint of u_{m+1}
+    // n_m; past the kept ones from the last of them
+    auto norm_of = [&](int m) {
+      const int k = m < NIT ? m : NIT - 1;
+      R n = sn[k][tid];
+      for (int j = k; j < m; ++j) {
+        R x, y, z;
+        inverse(n).apply(vx, vy, vz, x, y, z);
+        n = rsqrt_(x * x + y * y + z * z);
+      }
+      return n;
+    };
+    R bx = ux, by = uy, bz = uz;        // u_{m+1}
+    R ubx = uhx, uby = uhy, ubz = uhz;  // its adjoint
     vhx = 0.0; vhy = 0.0; vhz = 0.0;
     // only two contractions of the adjoints of A and B are needed:
     // aM = sum_m Xh_m : M^-1 and bM = sum_m n_m Xh_m : M^-1/2
-    R aM = 0.0, bM = 0.0;
+    R aM = 0.0, bM = 0.0, n = norm_of(p.an_iters - 1);
+    Adj X = inverse(n);
     for (int m = p.an_iters - 1; m >= 0; --m) {
-      R ax = vx, ay = vy, az = vz;  // u_m
-      for (int j = 0; j < m; ++j) solve(rsqrt_(ax * ax + ay * ay + az * az), vx, vy, vz, ax, ay, az);
-      const R n = rsqrt_(ax * ax + ay * ay + az * az);
-      R bx, by, bz, wx, wy, wz;
-      solve(n, vx, vy, vz, bx, by, bz);     // u_{m+1}
-      solve(n, ubx, uby, ubz, wx, wy, wz);  // X^-1 applied to the adjoint (X symmetric)
+      R wx, wy, wz;
+      X.apply(ubx, uby, ubz, wx, wy, wz);
       vhx += wx; vhy += wy; vhz += wz;
       const R Xh[6] = {-wx * bx, -wy * by, -wz * bz, -(wx * by + wy * bx), -(wx * bz + wz * bx),
                        -(wy * bz + wz * by)};
       R xi = 0.0, xh = 0.0;
 #pragma unroll
       for (int k = 0; k < 6; ++k) {
-        xi += Xh[k] * kc.Mi[k];
-        xh += Xh[k] * kc.Mh[k];
+        xi += Xh[k] * Mi[k];
+        xh += Xh[k] * Mh[k];
       }
       aM += xi;
       bM += n * xh;
       // d/dn of X = n B, contracted with Xh, then through n = |u_m|
       const R g = n > 0.0 ? hb * xh * fast_rcp(n) : 0.0;
-      ubx = g * ax; uby = g * ay; ubz = g * az;
+      if (m > 0) {
+        n = norm_of(m - 1);
+        X = inverse(n);
+        X.apply(vx, vy, vz, bx, by, bz);  // u_m
+      } else {
+        bx = vx; by = vy; bz = vz;        // u_0
+      }
+      ubx = g * bx; uby = g * by; ubz = g * bz;
     }
     vhx += ubx; vhy += uby; vhz += ubz;  // u_0 = v
     phh += aM * 0.5 * ddark;

@@ -505,9 +505,14 @@ struct Macro {
 // these mathematically (their extra terms are products with an exact zero and
 // the reciprocals of 1 are 1); the compiler fuses the remaining terms of the
 // two forms differently, so an output can differ in its last place.
-template <class R, bool AN = false, bool PF = false>
+// iterate(m, |u_m|) is called for every iterate of the anisotropic velocity.
+struct NoIterate {
+  template <class R>
+  __device__ __forceinline__ void operator()(int, R) const {}
+};
+template <class R, bool AN = false, bool PF = false, class It = NoIterate>
 __device__ __forceinline__ void macro_sums(const Params& p, float phx_f, const Sums<R>& s, float omega_prev,
-                                           Macro<R>& M) {
+                                           Macro<R>& M, It iterate = It{}) {
   static_assert(!(PF && AN), "the pure-fluid form is the isotropic one");
   const auto& kc = p.k<R>();
   const R phx = PF ? (R)1 : (R)phx_f;
@@ -543,6 +548,7 @@ __device__ __forceinline__ void macro_sums(const Params& p, float phx_f, const S
       ux = vx; uy = vy; uz = vz;
       for (int m = 0; m < p.an_iters; ++m) {
         const R un = rsqrt_(ux * ux + uy * uy + uz * uz);
+        iterate(m, un);
         R X[6];
 #pragma unroll
         for (int k = 0; k < 6; ++k) X[k] = rfma(un, Bm[k], Am[k]);
