@@ -72,32 +72,36 @@ void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, bool rec) {
   });
 }
 
-template <class S>
-void moments19(lbm_ctx* c, const lbm::Bufs& b, bool diag, float* rho, float* u, float* shear, float* omega,
-               float* sigma, float* tau) {
-  const uint32_t t = (uint32_t)c->t;
-  const dim3 grid(c->nblk), block(BLOCK);
+// The forms of k_moments and k_diag: shift, arithmetic, parity, anisotropy.
+template <class S, class Fn>
+void with_state_form(lbm_ctx* c, Fn&& fn) {
   with_shift(c->grid.shift_mode, [&](auto shw) {
-    constexpr bool SH = decltype(shw)::value;
     with_arith<S>(c->amode == 2 ? 2 : 0, [&](auto rt) {
-      using R = typename decltype(rt)::T;
       with_parity(c->t, [&](auto odd) {
-        constexpr bool OD = decltype(odd)::value;
-        const bool an = c->P.an_iters > 0;
-        if (diag && an)
-          hipLaunchKernelGGL((k_moments<S, SH, OD, true, R, true>), grid, block, 0, c->stream, c->P, b, t, c->nbox,
-                             rho, u, shear, omega, sigma, tau);
-        else if (diag)
-          hipLaunchKernelGGL((k_moments<S, SH, OD, true, R>), grid, block, 0, c->stream, c->P, b, t, c->nbox, rho, u,
-                             shear, omega, sigma, tau);
-        else if (an)
-          hipLaunchKernelGGL((k_moments<S, SH, OD, false, R, true>), grid, block, 0, c->stream, c->P, b, t, c->nbox,
-                             rho, u, shear, omega, sigma, tau);
-        else
-          hipLaunchKernelGGL((k_moments<S, SH, OD, false, R>), grid, block, 0, c->stream, c->P, b, t, c->nbox, rho,
-                             u, shear, omega, sigma, tau);
+        if (c->P.an_iters > 0) fn(shw, rt, odd, std::true_type{});
+        else fn(shw, rt, odd, std::false_type{});
       });
     });
+  });
+}
+
+template <class S>
+void moments19(lbm_ctx* c, const lbm::Bufs& b, float* rho, float* u, float* shear, float* omega, float* sigma,
+               float* tau) {
+  with_state_form<S>(c, [&](auto shw, auto rt, auto odd, auto an) {
+    hipLaunchKernelGGL((k_moments<S, decltype(shw)::value, decltype(odd)::value, typename decltype(rt)::T,
+                                  decltype(an)::value>),
+                       dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, b, (uint32_t)c->t, c->nbox, rho, u, shear,
+                       omega, sigma, tau);
+  });
+}
+
+template <class S>
+void diag19(lbm_ctx* c, const lbm::Bufs& b) {
+  with_state_form<S>(c, [&](auto shw, auto rt, auto odd, auto an) {
+    hipLaunchKernelGGL((k_diag<S, decltype(shw)::value, decltype(odd)::value, typename decltype(rt)::T,
+                               decltype(an)::value>),
+                       dim3(diag_blocks(c)), dim3(BLOCK), 0, c->stream, c->P, b, (uint32_t)c->t, diag_run(c));
   });
 }
 
@@ -130,7 +134,8 @@ void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src) {
 #define LBM_INSTANTIATE19(S)                                                                                    \
   namespace lbmrt {                                                                                             \
   template void step19<S>(lbm_ctx*, const lbm::Bufs&, int, bool);                                               \
-  template void moments19<S>(lbm_ctx*, const lbm::Bufs&, bool, float*, float*, float*, float*, float*, float*); \
+  template void moments19<S>(lbm_ctx*, const lbm::Bufs&, float*, float*, float*, float*, float*, float*);       \
+  template void diag19<S>(lbm_ctx*, const lbm::Bufs&);                                                          \
   template void init19<S>(lbm_ctx*, const lbm::Bufs&);                                                          \
   template void gather19<S>(lbm_ctx*, const lbm::Bufs&, float*);                                                \
   template void scatter19<S>(lbm_ctx*, const lbm::Bufs&, const float*);                                         \

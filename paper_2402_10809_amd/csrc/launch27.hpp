@@ -28,25 +28,30 @@ void step27(lbm_ctx* c, const lbm::q27::Bufs27& b, int diag) {
   });
 }
 
-template <class S>
-void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, bool diag, float* rho, float* u, float* shear, float* omega,
-               float* sigma, float* tau) {
-  const uint32_t t = (uint32_t)c->t;
-  const dim3 grid(c->nblk), block(BLOCK);
+template <class S, class Fn>
+void with_state_form27(lbm_ctx* c, Fn&& fn) {
   with_shift(c->grid.shift_mode, [&](auto shw) {
-    constexpr bool SH = decltype(shw)::value;
     with_arith<S>(c->amode == 2 ? 2 : 0, [&](auto rt) {
-      using R = typename decltype(rt)::T;
-      with_parity(c->t, [&](auto odd) {
-        constexpr bool OD = decltype(odd)::value;
-        if (diag)
-          hipLaunchKernelGGL((q27::k_moments<S, SH, OD, true, R>), grid, block, 0, c->stream, c->P, b, t, c->nbox,
-                             rho, u, shear, omega, sigma, tau);
-        else
-          hipLaunchKernelGGL((q27::k_moments<S, SH, OD, false, R>), grid, block, 0, c->stream, c->P, b, t, c->nbox,
-                             rho, u, shear, omega, sigma, tau);
-      });
+      with_parity(c->t, [&](auto odd) { fn(shw, rt, odd); });
     });
+  });
+}
+
+template <class S>
+void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, float* rho, float* u, float* shear, float* omega, float* sigma,
+               float* tau) {
+  with_state_form27<S>(c, [&](auto shw, auto rt, auto odd) {
+    hipLaunchKernelGGL((q27::k_moments<S, decltype(shw)::value, decltype(odd)::value, typename decltype(rt)::T>),
+                       dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, b, (uint32_t)c->t, c->nbox, rho, u, shear,
+                       omega, sigma, tau);
+  });
+}
+
+template <class S>
+void diag27(lbm_ctx* c, const lbm::q27::Bufs27& b) {
+  with_state_form27<S>(c, [&](auto shw, auto rt, auto odd) {
+    hipLaunchKernelGGL((q27::k_diag<S, decltype(shw)::value, decltype(odd)::value, typename decltype(rt)::T>),
+                       dim3(diag_blocks(c)), dim3(BLOCK), 0, c->stream, c->P, b, (uint32_t)c->t, diag_run(c));
   });
 }
 
@@ -79,8 +84,8 @@ void scatter27(lbm_ctx* c, const lbm::q27::Bufs27& b, const float* src) {
 #define LBM_INSTANTIATE27(S)                                                                                      \
   namespace lbmrt {                                                                                               \
   template void step27<S>(lbm_ctx*, const lbm::q27::Bufs27&, int);                                                \
-  template void moments27<S>(lbm_ctx*, const lbm::q27::Bufs27&, bool, float*, float*, float*, float*, float*,     \
-                             float*);                                                                             \
+  template void moments27<S>(lbm_ctx*, const lbm::q27::Bufs27&, float*, float*, float*, float*, float*, float*);   \
+  template void diag27<S>(lbm_ctx*, const lbm::q27::Bufs27&);                                                     \
   template void init27<S>(lbm_ctx*, const lbm::q27::Bufs27&);                                                     \
   template void gather27<S>(lbm_ctx*, const lbm::q27::Bufs27&, float*);                                           \
   template void scatter27<S>(lbm_ctx*, const lbm::q27::Bufs27&, const float*);                                    \

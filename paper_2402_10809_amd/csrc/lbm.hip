@@ -388,19 +388,28 @@ lbm_status check_stable(lbm_ctx* c, const double* dg) {
   return LBM_OK;
 }
 
+lbm_status moments_launch(lbm_ctx* c, float* rho, float* u, float* shear, float* omega, float* sigma, float* tau) {
+  with_storage(c->grid.storage, [&](auto tag) {
+    using S = typename decltype(tag)::T;
+    if (c->q == 27) moments27<S>(c, bufs27(c), rho, u, shear, omega, sigma, tau);
+    else moments19<S>(c, bufs(c), rho, u, shear, omega, sigma, tau);
+  });
+  HIP_TRY(c, hipGetLastError());
+  return LBM_OK;
+}
+
 // part: where the diagnostics partials go (nullptr: the workspace's area)
-lbm_status moments_launch(lbm_ctx* c, bool diag, float* rho, float* u, float* shear, float* omega, float* sigma,
-                          float* tau, double* part = nullptr) {
+lbm_status diag_launch(lbm_ctx* c, double* part = nullptr) {
   with_storage(c->grid.storage, [&](auto tag) {
     using S = typename decltype(tag)::T;
     if (c->q == 27) {
       q27::Bufs27 b = bufs27(c);
       if (part) b.part = part;
-      moments27<S>(c, b, diag, rho, u, shear, omega, sigma, tau);
+      diag27<S>(c, b);
     } else {
       Bufs b = bufs(c);
       if (part) b.part = part;
-      moments19<S>(c, b, diag, rho, u, shear, omega, sigma, tau);
+      diag19<S>(c, b);
     }
   });
   HIP_TRY(c, hipGetLastError());
@@ -623,16 +632,16 @@ lbm_status lbm_moments(lbm_ctx* c, float* rho, float* u, float* shear, float* om
   if (omega) HIP_TRY(c, hipMemsetAsync(omega, 0, nb, c->stream));
   if (sigma) HIP_TRY(c, hipMemsetAsync(sigma, 0, 6 * nb, c->stream));
   if (tau) HIP_TRY(c, hipMemsetAsync(tau, 0, 3 * nb, c->stream));
-  return moments_launch(c, false, rho, u, shear, omega, sigma, tau);
+  return moments_launch(c, rho, u, shear, omega, sigma, tau);
 }
 
 lbm_status lbm_diagnostics(lbm_ctx* c, double* out) {
   CTX_CHECK(c);
   if (!out) return fail(LBM_E_INVALID, "out is NULL");
-  lbm_status s = moments_launch(c, true, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+  lbm_status s = diag_launch(c);
   if (s != LBM_OK) return s;
   double dg[NDIAGP];
-  s = read_diag(c, c->nblk, dg);
+  s = read_diag(c, diag_blocks(c), dg);
   if (s != LBM_OK) return s;
   for (int k = 0; k < 10; ++k) out[k] = dg[k];
   out[10] = (double)c->t;
@@ -653,12 +662,12 @@ lbm_status lbm_diagnostics_noalloc(lbm_ctx* c, double* out) {
   void* base = nullptr;
   lbm_status s = scratch_address(c->device, &base);
   if (s != LBM_OK) return s;
-  double* part = (double*)base;                      // every block writes all its partials
+  double* part = (double*)base;                      // every workgroup writes all its partials
   double* dout = (double*)((char*)base + part_bytes);
-  s = moments_launch(c, true, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, part);
+  s = diag_launch(c, part);
   if (s != LBM_OK) return s;
   double dg[NDIAGP];
-  s = finalize(c, part, c->nblk, NDIAGP, DIAG_OPS, dg, dout);
+  s = finalize(c, part, diag_blocks(c), NDIAGP, DIAG_OPS, dg, dout);
   if (s != LBM_OK) return s;
   for (int k = 0; k < 10; ++k) out[k] = dg[k];
   out[10] = (double)c->t;

@@ -145,17 +145,24 @@ lbm::q27::Bufs27 bufs27(lbm_ctx* c);
 // wall shear stress, accumulated into the objective partials; rec: record
 // the step for the adjoint (FP32 storage, shift mode 0 only).
 template <class S> void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, bool rec);
-template <class S> void moments19(lbm_ctx* c, const lbm::Bufs& b, bool diag, float* rho, float* u, float* shear,
-                                  float* omega, float* sigma, float* tau);
+template <class S> void moments19(lbm_ctx* c, const lbm::Bufs& b, float* rho, float* u, float* shear, float* omega,
+                                  float* sigma, float* tau);
+template <class S> void diag19(lbm_ctx* c, const lbm::Bufs& b);
 template <class S> void init19(lbm_ctx* c, const lbm::Bufs& b);
 template <class S> void gather19(lbm_ctx* c, const lbm::Bufs& b, float* dst);
 template <class S> void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src);
 template <class S> void step27(lbm_ctx* c, const lbm::q27::Bufs27& b, int diag);
-template <class S> void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, bool diag, float* rho, float* u,
-                                  float* shear, float* omega, float* sigma, float* tau);
+template <class S> void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, float* rho, float* u, float* shear,
+                                  float* omega, float* sigma, float* tau);
+template <class S> void diag27(lbm_ctx* c, const lbm::q27::Bufs27& b);
 template <class S> void init27(lbm_ctx* c, const lbm::q27::Bufs27& b);
 template <class S> void gather27(lbm_ctx* c, const lbm::q27::Bufs27& b, float* dst);
 template <class S> void scatter27(lbm_ctx* c, const lbm::q27::Bufs27& b, const float* src);
+
+// Blocks of 256 cells per workgroup of k_diag, and its workgroups (no more
+// than the context's blocks, whose partial rows the workspace holds).
+inline uint32_t diag_run(const lbm_ctx* c) { return (uint32_t)((c->nblk + DIAG_BLOCKS - 1) / DIAG_BLOCKS); }
+inline int diag_blocks(const lbm_ctx* c) { return (c->nblk + (int)diag_run(c) - 1) / (int)diag_run(c); }
 
 // Storage dispatch for the per-storage launch functions.
 template <class Fn>

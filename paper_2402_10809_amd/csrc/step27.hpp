@@ -444,16 +444,14 @@ __global__ __launch_bounds__(NT) void k_step(Params p, Bufs27 b) {
   if (blockIdx.x == 0 && threadIdx.x == 0) b.tc[ODD ? 0 : 1] = t + 1u;
 }
 
-// Moments of the current state (dense box outputs, any may be null) and
-// optionally the diagnostics partials.
-template <class S, bool SHW, bool ODD, bool DIAG, class R>
+// Moments of the current state (dense box outputs, any may be null).
+template <class S, bool SHW, bool ODD, class R>
 __global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs27 b, uint32_t t, size_t nbox, float* rho_o,
                                                     float* u_o, float* shear_o, float* omega_o, float* sigma_o,
                                                     float* tau_o) {
   const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
   const uint64_t lk = c < (uint32_t)p.nc ? b.links[c] : L_DEAD;
   const bool active = !(lk & L_DEAD);
-  double dv[NDIAGP];
   if (active) {
     Pos q = position(p, c, b.code[c]);
     if (ODD) load_deltas(b.delta, q);
@@ -484,16 +482,33 @@ __global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs27 b, uint32_t 
 #pragma unroll
       for (int a = 0; a < 3; ++a) tau_o[(size_t)a * nbox + idx] = (float)tw[a];
     }
-    if (DIAG) diag_terms<R>(p, phx, d, M, lk, true, dv);
-  } else if (DIAG) {
-    float d[Q] = {};
-    Macro<R> M{};
-    diag_terms<R>(p, 0.f, d, M, uint64_t(0), false, dv);
   }
-  if (DIAG) {
-    const int ops[NDIAGP] = {0, 0, 0, 0, 0, 0, 1, 2, 1, 0, 0};
-    block_reduce<NDIAGP>(dv, ops, b.part + (size_t)blockIdx.x * NDIAGP);
+}
+
+// Diagnostics of the current state (see step.hpp's k_diag).
+template <class S, bool SHW, bool ODD, class R>
+__global__ __launch_bounds__(BLOCK) void k_diag(Params p, Bufs27 b, uint32_t t, uint32_t per) {
+  double acc[NDIAGP];
+  diag_start(acc);
+  const uint32_t base = xcd_block(blockIdx.x, gridDim.x) * per * BLOCK + threadIdx.x;
+  for (uint32_t i = 0; i < per; ++i) {
+    const uint32_t c = base + i * BLOCK;
+    const uint64_t lk = c < (uint32_t)p.nc ? b.links[c] : L_DEAD;
+    if (lk & L_DEAD) continue;
+    Pos q = position(p, c, b.code[c]);
+    if (ODD) load_deltas(b.delta, q);
+    const float phx = ldo(b.phi, c);
+    float d[Q], pt[Q];
+    pull<S, SHW, true, ODD>(p, Pop<S>(b.A, p.abytes), b.phi, c, lk, q, phx, d, pt);
+    open_fill(p, q.row, lk, t, b.shape, b.wave, b.side + (ODD ? (size_t)p.nrow * 18 : 0), d);
+    Macro<R> M;
+    macro_sums<R>(p, phx, moment_sums<R>(d), b.omega[c], M);
+    double v[NDIAGP];
+    diag_terms<R>(p, phx, d, M, lk, true, v);
+    diag_add(acc, v);
   }
+  const int ops[NDIAGP] = {0, 0, 0, 0, 0, 0, 1, 2, 1, 0, 0};
+  block_reduce<NDIAGP>(acc, ops, b.part + (size_t)blockIdx.x * NDIAGP);
 }
 
 // Rest state at even parity (see step.hpp's k_init).
