@@ -86,13 +86,12 @@ void with_state_form(lbm_ctx* c, Fn&& fn) {
 }
 
 template <class S>
-void moments19(lbm_ctx* c, const lbm::Bufs& b, float* rho, float* u, float* shear, float* omega, float* sigma,
-               float* tau) {
+void moments19(lbm_ctx* c, const lbm::Bufs& b, const lbm::Dense& out) {
   with_state_form<S>(c, [&](auto shw, auto rt, auto odd, auto an) {
     hipLaunchKernelGGL((k_moments<S, decltype(shw)::value, decltype(odd)::value, typename decltype(rt)::T,
                                   decltype(an)::value>),
-                       dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, b, (uint32_t)c->t, c->nbox, rho, u, shear,
-                       omega, sigma, tau);
+                       dim3(c->nblk + dense_blocks(out)), dim3(BLOCK), 0, c->stream, c->P, b, (uint32_t)c->t,
+                       (uint32_t)c->nblk, out);
   });
 }
 
@@ -134,7 +133,7 @@ void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src) {
 #define LBM_INSTANTIATE19(S)                                                                                    \
   namespace lbmrt {                                                                                             \
   template void step19<S>(lbm_ctx*, const lbm::Bufs&, int, bool);                                               \
-  template void moments19<S>(lbm_ctx*, const lbm::Bufs&, float*, float*, float*, float*, float*, float*);       \
+  template void moments19<S>(lbm_ctx*, const lbm::Bufs&, const lbm::Dense&);                                    \
   template void diag19<S>(lbm_ctx*, const lbm::Bufs&);                                                          \
   template void init19<S>(lbm_ctx*, const lbm::Bufs&);                                                          \
   template void gather19<S>(lbm_ctx*, const lbm::Bufs&, float*);                                                \

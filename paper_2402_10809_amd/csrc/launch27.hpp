@@ -38,12 +38,11 @@ void with_state_form27(lbm_ctx* c, Fn&& fn) {
 }
 
 template <class S>
-void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, float* rho, float* u, float* shear, float* omega, float* sigma,
-               float* tau) {
+void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, const lbm::Dense& out) {
   with_state_form27<S>(c, [&](auto shw, auto rt, auto odd) {
     hipLaunchKernelGGL((q27::k_moments<S, decltype(shw)::value, decltype(odd)::value, typename decltype(rt)::T>),
-                       dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, b, (uint32_t)c->t, c->nbox, rho, u, shear,
-                       omega, sigma, tau);
+                       dim3(c->nblk + dense_blocks(out)), dim3(BLOCK), 0, c->stream, c->P, b, (uint32_t)c->t,
+                       (uint32_t)c->nblk, out);
   });
 }
 
@@ -84,7 +83,7 @@ void scatter27(lbm_ctx* c, const lbm::q27::Bufs27& b, const float* src) {
 #define LBM_INSTANTIATE27(S)                                                                                      \
   namespace lbmrt {                                                                                               \
   template void step27<S>(lbm_ctx*, const lbm::q27::Bufs27&, int);                                                \
-  template void moments27<S>(lbm_ctx*, const lbm::q27::Bufs27&, float*, float*, float*, float*, float*, float*);   \
+  template void moments27<S>(lbm_ctx*, const lbm::q27::Bufs27&, const lbm::Dense&);                               \
   template void diag27<S>(lbm_ctx*, const lbm::q27::Bufs27&);                                                     \
   template void init27<S>(lbm_ctx*, const lbm::q27::Bufs27&);                                                     \
   template void gather27<S>(lbm_ctx*, const lbm::q27::Bufs27&, float*);                                           \

@@ -46,6 +46,7 @@ struct HostLayout {
   std::vector<uint8_t> solid;     // the mask, box layout
   std::vector<uint32_t> code;     // per compact cell
   std::vector<uint32_t> rowbox;   // box index of (x = 0) of each row
+  std::vector<int> lines;         // [nz][ny][2]: x range of the line's row (empty: 0, 0)
   std::vector<int> delta;         // [nrow][8]: compact start - first x of the neighbour row of pair k
   std::vector<int> rel;           // [nrow][8]: delta minus (compact start - first x) of the row itself
   std::vector<int64_t> fluid_box; // box index per fluid cell (ascending)
@@ -99,6 +100,7 @@ inline void build_host_layout(HostLayout& L, const lbm_grid& g, const uint8_t* s
   L.xbits = xb;
   L.code.assign(L.nc, 0u);
   L.rowbox.assign(L.nrow, 0u);
+  L.lines.assign((size_t)g.ny * g.nz * 2, 0);
   L.delta.assign((size_t)L.nrow * 8, 0);
   L.rel.assign((size_t)L.nrow * 8, 0);
   std::vector<int64_t> rowid((size_t)g.ny * g.nz, -1);
@@ -111,6 +113,8 @@ inline void build_host_layout(HostLayout& L, const lbm_grid& g, const uint8_t* s
     rowid[(size_t)z * g.ny + y] = r;
     const size_t base = ((size_t)z * g.ny + y) * nx;
     L.rowbox[r] = (uint32_t)base;
+    L.lines[((size_t)z * g.ny + y) * 2] = L.rows.x0[r];
+    L.lines[((size_t)z * g.ny + y) * 2 + 1] = L.rows.x1[r];
     for (int x = L.rows.x0[r]; x < L.rows.x1[r]; ++x) {
       const int64_t ci = L.rows.cb[r] + x - L.rows.x0[r];
       L.code[ci] = ((uint32_t)r << xb) | (uint32_t)x;

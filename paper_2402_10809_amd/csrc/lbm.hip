@@ -41,6 +41,7 @@ using namespace lbmrt;
 
 namespace {
 
+constexpr size_t DENSE_CACHED = INFINITY_CACHE_BYTES;  // dense outputs written in one launch (k_moments)
 constexpr int CHECK_EVERY = 1000;                       // steps between stability checks
 constexpr double MAX_SPEED = 0.3 / 1.7320508075688772;  // 0.3 c_s
 
@@ -122,6 +123,7 @@ Layout make_layout(const lbm_grid& g, int64_t nc, int64_t nrow, int T, int ckpt)
   L.winfo = take((size_t)wave_records(nc) * sizeof(lbm::WaveInfo));
   L.shape = take((size_t)nrow * 4);
   L.rowbox = take((size_t)nrow * 4);
+  L.lines = take((size_t)g.ny * g.nz * 8);
   L.stage = take((size_t)(q + 1) * nc * 4);
   const size_t nbmax = (size_t)blocks_for_nt(nc, STEP_NT_MIN);  // most blocks any launch uses
   L.part = take(nbmax * NDIAGP * 8);
@@ -388,11 +390,11 @@ lbm_status check_stable(lbm_ctx* c, const double* dg) {
   return LBM_OK;
 }
 
-lbm_status moments_launch(lbm_ctx* c, float* rho, float* u, float* shear, float* omega, float* sigma, float* tau) {
+lbm_status moments_launch(lbm_ctx* c, const Dense& out) {
   with_storage(c->grid.storage, [&](auto tag) {
     using S = typename decltype(tag)::T;
-    if (c->q == 27) moments27<S>(c, bufs27(c), rho, u, shear, omega, sigma, tau);
-    else moments19<S>(c, bufs(c), rho, u, shear, omega, sigma, tau);
+    if (c->q == 27) moments27<S>(c, bufs27(c), out);
+    else moments19<S>(c, bufs(c), out);
   });
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;
@@ -590,6 +592,7 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* solid, const float* p
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.delta, c->delta.data(), c->delta.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.rel, c->rel.data(), c->rel.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.shape, shape.data(), shape.size() * 4, hipMemcpyHostToDevice, c->stream));
+  HIP_TRY0(hipMemcpyAsync(c->ws + c->L.lines, c->lines.data(), c->lines.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.rowbox, c->rowbox.data(), c->rowbox.size() * 4, hipMemcpyHostToDevice, c->stream));
   if (P.in_table > 0)
     HIP_TRY0(hipMemcpyAsync(c->ws + c->L.wave, op->wave_table, (size_t)P.in_table * sizeof(double),
@@ -625,14 +628,39 @@ lbm_status lbm_step(lbm_ctx* c, int n) {
 
 lbm_status lbm_moments(lbm_ctx* c, float* rho, float* u, float* shear, float* omega, float* sigma, float* tau) {
   CTX_CHECK(c);
-  const size_t nb = c->nbox * 4;
-  if (rho) HIP_TRY(c, hipMemsetAsync(rho, 0, nb, c->stream));
-  if (u) HIP_TRY(c, hipMemsetAsync(u, 0, 3 * nb, c->stream));
-  if (shear) HIP_TRY(c, hipMemsetAsync(shear, 0, nb, c->stream));
-  if (omega) HIP_TRY(c, hipMemsetAsync(omega, 0, nb, c->stream));
-  if (sigma) HIP_TRY(c, hipMemsetAsync(sigma, 0, 6 * nb, c->stream));
-  if (tau) HIP_TRY(c, hipMemsetAsync(tau, 0, 3 * nb, c->stream));
-  return moments_launch(c, rho, u, shear, omega, sigma, tau);
+  Dense d{};
+  auto planes = [&](float* at, int first, int n) {
+    for (int k = 0; at && k < n; ++k) d.o[first + k] = at + (size_t)k * c->nbox;
+  };
+  planes(rho, 0, 1);
+  planes(u, 1, 3);
+  planes(shear, 4, 1);
+  planes(omega, 5, 1);
+  planes(sigma, 6, 6);
+  planes(tau, 12, 3);
+  d.lines = (const int2*)(c->ws + c->L.lines);
+  d.nbox = (uint32_t)c->nbox;
+  d.vec = c->P.nx % 4 == 0;
+  size_t bytes = 0;
+  for (const float* o : d.o) {
+    if (!o) continue;
+    bytes += c->nbox * 4;
+    d.vec = d.vec && ((uintptr_t)o & 15) == 0;
+  }
+  if ((size_t)c->nc < c->nbox) {  // else the rows cover the box
+    // the zeros outside the rows: see k_moments
+    d.rest = bytes <= DENSE_CACHED;
+    if (!d.rest) {
+      const size_t nb = c->nbox * 4;
+      if (rho) HIP_TRY(c, hipMemsetAsync(rho, 0, nb, c->stream));
+      if (u) HIP_TRY(c, hipMemsetAsync(u, 0, 3 * nb, c->stream));
+      if (shear) HIP_TRY(c, hipMemsetAsync(shear, 0, nb, c->stream));
+      if (omega) HIP_TRY(c, hipMemsetAsync(omega, 0, nb, c->stream));
+      if (sigma) HIP_TRY(c, hipMemsetAsync(sigma, 0, 6 * nb, c->stream));
+      if (tau) HIP_TRY(c, hipMemsetAsync(tau, 0, 3 * nb, c->stream));
+    }
+  }
+  return moments_launch(c, d);
 }
 
 lbm_status lbm_diagnostics(lbm_ctx* c, double* out) {

@@ -39,7 +39,7 @@ constexpr size_t INFINITY_CACHE_BYTES = (size_t)256 << 20;
 inline int step_nt(int storage) { return storage == LBM_STORE_FP32 ? 256 : STEP_NT16; }
 
 struct Layout {
-  size_t A, code, links, phi, omega, delta, rel, winfo, shape, rowbox, stage, part, diag, obj, tc, wave, side;
+  size_t A, code, links, phi, omega, delta, rel, winfo, shape, rowbox, lines, stage, part, diag, obj, tc, wave, side;
   // adjoint
   size_t ck, rec, rho, ah, omh, phih, aside;
   int nck, ckpt, T;
@@ -145,19 +145,22 @@ lbm::q27::Bufs27 bufs27(lbm_ctx* c);
 // wall shear stress, accumulated into the objective partials; rec: record
 // the step for the adjoint (FP32 storage, shift mode 0 only).
 template <class S> void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, bool rec);
-template <class S> void moments19(lbm_ctx* c, const lbm::Bufs& b, float* rho, float* u, float* shear, float* omega,
-                                  float* sigma, float* tau);
+template <class S> void moments19(lbm_ctx* c, const lbm::Bufs& b, const lbm::Dense& out);
 template <class S> void diag19(lbm_ctx* c, const lbm::Bufs& b);
 template <class S> void init19(lbm_ctx* c, const lbm::Bufs& b);
 template <class S> void gather19(lbm_ctx* c, const lbm::Bufs& b, float* dst);
 template <class S> void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src);
 template <class S> void step27(lbm_ctx* c, const lbm::q27::Bufs27& b, int diag);
-template <class S> void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, float* rho, float* u, float* shear,
-                                  float* omega, float* sigma, float* tau);
+template <class S> void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, const lbm::Dense& out);
 template <class S> void diag27(lbm_ctx* c, const lbm::q27::Bufs27& b);
 template <class S> void init27(lbm_ctx* c, const lbm::q27::Bufs27& b);
 template <class S> void gather27(lbm_ctx* c, const lbm::q27::Bufs27& b, float* dst);
 template <class S> void scatter27(lbm_ctx* c, const lbm::q27::Bufs27& b, const float* src);
+
+// Workgroups of k_moments outside the rows.
+inline unsigned dense_blocks(const lbm::Dense& out) {
+  return out.rest ? (out.nbox + lbm::DENSE_REST - 1) / lbm::DENSE_REST : 0u;
+}
 
 // Blocks of 256 cells per workgroup of k_diag, and its workgroups (no more
 // than the context's blocks, whose partial rows the workspace holds).

@@ -1202,46 +1202,111 @@ void k_step(Params p, Bufs b) {
   if (blockIdx.x == 0 && threadIdx.x == 0) b.tc[ODD ? 0 : 1] = t + 1u;
 }
 
-// Moments of the current state (no collision): dense box outputs (any may be
-// null).
-template <class S, bool SHW, bool ODD, class R, bool AN = false>
-__global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs b, uint32_t t, size_t nbox, float* rho_o,
-                                                    float* u_o, float* shear_o, float* omega_o, float* sigma_o,
-                                                    float* tau_o) {
-  const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
-  const uint32_t lk = c < (uint32_t)p.nc ? b.links[c] : LK_DEAD;
-  const bool active = !(lk & LK_DEAD);
-  if (active) {
-    Pos q = position(p, c, b.code[c]);
-    if (ODD) load_deltas(b.delta, q);
-    const float phx = ldo(b.phi, c);
-    float d[Q], pt[Q];
-    pull<S, SHW, true, ODD>(p, Pop<S>(b.A, p.abytes), b.phi, c, lk, q, phx, d, pt);
-    open_fill(p, q.row, lk, t, b.shape, b.wave, b.side + (ODD ? (size_t)p.nrow * 10 : 0), d);
-    Macro<R> M;
-    macro<R, AN>(p, phx, d, b.omega[c], M);
-    const size_t idx = (size_t)b.rowbox[q.row] + (size_t)q.x;
-    if (rho_o) rho_o[idx] = (float)M.rho;
-    if (u_o) {
-      u_o[idx] = (float)M.ux;
-      u_o[nbox + idx] = (float)M.uy;
-      u_o[2 * nbox + idx] = (float)M.uz;
-    }
-    if (shear_o) shear_o[idx] = M.shear;
-    if (omega_o) omega_o[idx] = (float)M.omega;
-    if (sigma_o) {
-      const R s = (R)0.5 * M.omega - (R)1;
+// Dense box outputs: the planes of rho, u, shear, omega, sigma and tau (null
+// where not asked for), and per (z, y) line of the box the x range [x, y) that
+// its compact row covers.
+constexpr int NDENSE = 15;
+struct Dense {
+  float* o[NDENSE];    // rho; u x y z; shear; omega; sigma xx yy zz xy xz yz; tau x y z
+  const int2* lines;   // [nz][ny]
+  uint32_t nbox;         // voxels
+  int rest;              // whether this launch writes the zeros outside the rows
+  int vec;               // four voxels at a time there: nx % 4 == 0 and every plane on 16 bytes
+};
+constexpr uint32_t DENSE_REST = 16 * BLOCK;  // voxels per workgroup of that part
+
+// Zeros outside the rows, all planes of DENSE_REST voxels, VEC voxels at a time (4
+// where four of them lie in one line and start on 16 bytes in every plane).
+template <int VEC>
+__device__ __forceinline__ void dense_rest(const Params& p, const Dense& out, uint32_t part) {
+  typedef float vec __attribute__((ext_vector_type(VEC)));
+  const uint32_t nx = (uint32_t)p.nx, b0 = part * DENSE_REST;
+  for (uint32_t k = threadIdx.x * VEC; k < DENSE_REST; k += BLOCK * VEC) {
+    const uint32_t v = b0 + k;
+    if (v >= out.nbox) return;
+    const uint32_t line = v / nx;
+    const int x = (int)(v - line * nx);
+    const int2 r = out.lines[line];
+    if (x + VEC <= r.x || x >= r.y) {
 #pragma unroll
-      for (int k = 0; k < 6; ++k) sigma_o[(size_t)k * nbox + idx] = (float)(s * M.P[k]);
-    }
-    if (tau_o) {
-      float n[3];
-      R tw[3] = {(R)0, (R)0, (R)0};
-      if (wall_normal(lk, n)) wall_tau(M, n, tw);
+      for (int i = 0; i < NDENSE; ++i)
+        if (out.o[i]) *(vec*)(out.o[i] + v) = (vec)0.0f;
+    } else if (VEC > 1) {
+      for (int j = 0; j < VEC; ++j)
+        if (x + j < r.x || x + j >= r.y)
 #pragma unroll
-      for (int a = 0; a < 3; ++a) tau_o[(size_t)a * nbox + idx] = (float)tw[a];
+          for (int i = 0; i < NDENSE; ++i)
+            if (out.o[i]) out.o[i][v + j] = 0.0f;
     }
   }
+}
+
+// The dense values of a fluid cell at box voxel idx.
+template <class R, class LK>
+__device__ __forceinline__ void dense_cell(const Dense& out, size_t idx, const Macro<R>& M, LK&& normal) {
+  auto put = [&](int i, float v) { if (out.o[i]) out.o[i][idx] = v; };
+  put(0, (float)M.rho);
+  put(1, (float)M.ux);
+  put(2, (float)M.uy);
+  put(3, (float)M.uz);
+  put(4, M.shear);
+  put(5, (float)M.omega);
+  if (out.o[6]) {
+    const R s = (R)0.5 * M.omega - (R)1;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) put(6 + k, (float)(s * M.P[k]));
+  }
+  if (out.o[12]) {
+    float n[3];
+    R tw[3] = {(R)0, (R)0, (R)0};
+    if (normal(n)) wall_tau(M, n, tw);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) put(12 + a, (float)tw[a]);
+  }
+}
+// Solid voxels inside a row's range.
+__device__ __forceinline__ void dense_dead(const Dense& out, size_t idx) {
+#pragma unroll
+  for (int i = 0; i < NDENSE; ++i)
+    if (out.o[i]) out.o[i][idx] = 0.0f;
+}
+
+// Moments of the current state (no collision) as dense box outputs: the first
+// workgroups (one per 256 compact cells) write the rows, dead slots as zeros;
+// with out.rest the others write the zeros outside the rows, so that every voxel
+// of every plane is written once in one launch.
+// That is for outputs that fit the Infinity Cache (DENSE_CACHED bytes, the
+// launch in lbm_moments), where clearing the planes first costs a launch of 3 to
+// 12 us each: rho, u, shear, omega, tau of 192x128x128 (113 MB) 37 -> 20 us, of
+// 203x131x117 (112 MB, odd sizes, D3Q27) 43 -> 19 us, rho, u, shear, omega of
+// 32^3 11 -> 4.5 us.  Beyond it the writes to memory bound it (512x320x320, 1.9 GB:
+// one launch 397 us, clears and cells 286 + 103 us; the zeros plane by plane in
+// the same launch, in 64 KB chunks 466 us, in one moving window 428 us), and the
+// planes are cleared first.
+template <class S, bool SHW, bool ODD, class R, bool AN>
+__global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs b, uint32_t t, uint32_t nblk, Dense out) {
+  if (blockIdx.x >= nblk) {
+    if (out.vec) dense_rest<4>(p, out, blockIdx.x - nblk);
+    else dense_rest<1>(p, out, blockIdx.x - nblk);
+    return;
+  }
+  const uint32_t c = xcd_block(blockIdx.x, nblk) * BLOCK + threadIdx.x;
+  if (c >= (uint32_t)p.nc) return;
+  const uint32_t lk = b.links[c];
+  Pos q = position(p, c, b.code[c]);
+  const size_t idx = (size_t)b.rowbox[q.row] + (size_t)q.x;
+  if (lk & LK_DEAD) {
+    dense_dead(out, idx);
+    return;
+  }
+  if (ODD) load_deltas(b.delta, q);
+  const float phx = ldo(b.phi, c);
+  float d[Q], pt[Q];
+  pull<S, SHW, true, ODD>(p, Pop<S>(b.A, p.abytes), b.phi, c, lk, q, phx, d, pt);
+  open_fill(p, q.row, lk, t, b.shape, b.wave, b.side + (ODD ? (size_t)p.nrow * 10 : 0), d);
+  Macro<R> M;
+  macro_sums<R, AN>(p, phx, moment_sums<R>(d), b.omega[c], M);
+  dense_cell(out, idx, M, [&](float (&n)[3]) { return wall_normal(lk, n); });
 }
 
 // Diagnostics of the current state (no collision): each workgroup sums a

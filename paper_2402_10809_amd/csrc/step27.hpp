@@ -444,45 +444,31 @@ __global__ __launch_bounds__(NT) void k_step(Params p, Bufs27 b) {
   if (blockIdx.x == 0 && threadIdx.x == 0) b.tc[ODD ? 0 : 1] = t + 1u;
 }
 
-// Moments of the current state (dense box outputs, any may be null).
+// Moments of the current state as dense box outputs (see step.hpp's k_moments).
 template <class S, bool SHW, bool ODD, class R>
-__global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs27 b, uint32_t t, size_t nbox, float* rho_o,
-                                                    float* u_o, float* shear_o, float* omega_o, float* sigma_o,
-                                                    float* tau_o) {
-  const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
-  const uint64_t lk = c < (uint32_t)p.nc ? b.links[c] : L_DEAD;
-  const bool active = !(lk & L_DEAD);
-  if (active) {
-    Pos q = position(p, c, b.code[c]);
-    if (ODD) load_deltas(b.delta, q);
-    const float phx = ldo(b.phi, c);
-    float d[Q], pt[Q];
-    pull<S, SHW, true, ODD>(p, Pop<S>(b.A, p.abytes), b.phi, c, lk, q, phx, d, pt);
-    open_fill(p, q.row, lk, t, b.shape, b.wave, b.side + (ODD ? (size_t)p.nrow * 18 : 0), d);
-    Macro<R> M;
-    macro_sums<R>(p, phx, moment_sums<R>(d), b.omega[c], M);
-    const size_t idx = (size_t)b.rowbox[q.row] + (size_t)q.x;
-    if (rho_o) rho_o[idx] = (float)M.rho;
-    if (u_o) {
-      u_o[idx] = (float)M.ux;
-      u_o[nbox + idx] = (float)M.uy;
-      u_o[2 * nbox + idx] = (float)M.uz;
-    }
-    if (shear_o) shear_o[idx] = M.shear;
-    if (omega_o) omega_o[idx] = (float)M.omega;
-    if (sigma_o) {
-      const R s = (R)0.5 * M.omega - (R)1;
-#pragma unroll
-      for (int k = 0; k < 6; ++k) sigma_o[(size_t)k * nbox + idx] = (float)(s * M.P[k]);
-    }
-    if (tau_o) {
-      float n[3];
-      R tw[3] = {(R)0, (R)0, (R)0};
-      if (wall_normal(lk, n)) wall_tau(M, n, tw);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) tau_o[(size_t)a * nbox + idx] = (float)tw[a];
-    }
+__global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs27 b, uint32_t t, uint32_t nblk, Dense out) {
+  if (blockIdx.x >= nblk) {
+    if (out.vec) dense_rest<4>(p, out, blockIdx.x - nblk);
+    else dense_rest<1>(p, out, blockIdx.x - nblk);
+    return;
   }
+  const uint32_t c = xcd_block(blockIdx.x, nblk) * BLOCK + threadIdx.x;
+  if (c >= (uint32_t)p.nc) return;
+  const uint64_t lk = b.links[c];
+  Pos q = position(p, c, b.code[c]);
+  const size_t idx = (size_t)b.rowbox[q.row] + (size_t)q.x;
+  if (lk & L_DEAD) {
+    dense_dead(out, idx);
+    return;
+  }
+  if (ODD) load_deltas(b.delta, q);
+  const float phx = ldo(b.phi, c);
+  float d[Q], pt[Q];
+  pull<S, SHW, true, ODD>(p, Pop<S>(b.A, p.abytes), b.phi, c, lk, q, phx, d, pt);
+  open_fill(p, q.row, lk, t, b.shape, b.wave, b.side + (ODD ? (size_t)p.nrow * 18 : 0), d);
+  Macro<R> M;
+  macro_sums<R>(p, phx, moment_sums<R>(d), b.omega[c], M);
+  dense_cell(out, idx, M, [&](float (&n)[3]) { return wall_normal(lk, n); });
 }
 
 // Diagnostics of the current state (see step.hpp's k_diag).
