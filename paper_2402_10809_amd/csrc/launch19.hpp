@@ -128,6 +128,26 @@ void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src) {
   });
 }
 
+template <class S>
+void state_out19(lbm_ctx* c, const lbm::Bufs& b, double* f, float* omega, int i0, int i1) {
+  with_shift(c->grid.shift_mode, [&](auto shw) {
+    with_parity(c->t, [&](auto odd) {
+      hipLaunchKernelGGL((k_state_out<S, decltype(shw)::value, decltype(odd)::value>), dim3(c->nblk), dim3(BLOCK), 0,
+                         c->stream, c->P, b, (const uint32_t*)(c->ws + c->L.wrank), f, omega, i0, i1, (uint32_t)c->nf);
+    });
+  });
+}
+
+template <class S>
+void state_in19(lbm_ctx* c, const lbm::Bufs& b, const double* f, const float* omega, int i0, int i1) {
+  with_shift(c->grid.shift_mode, [&](auto shw) {
+    with_parity(c->t, [&](auto odd) {
+      hipLaunchKernelGGL((k_state_in<S, decltype(shw)::value, decltype(odd)::value>), dim3(c->nblk), dim3(BLOCK), 0,
+                         c->stream, c->P, b, (const uint32_t*)(c->ws + c->L.wrank), f, omega, i0, i1, (uint32_t)c->nf);
+    });
+  });
+}
+
 }  // namespace lbmrt
 
 #define LBM_INSTANTIATE19(S)                                                                                    \
@@ -136,6 +156,8 @@ void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src) {
   template void moments19<S>(lbm_ctx*, const lbm::Bufs&, const lbm::Dense&);                                    \
   template void diag19<S>(lbm_ctx*, const lbm::Bufs&);                                                          \
   template void init19<S>(lbm_ctx*, const lbm::Bufs&);                                                          \
+  template void state_out19<S>(lbm_ctx*, const lbm::Bufs&, double*, float*, int, int); \
+  template void state_in19<S>(lbm_ctx*, const lbm::Bufs&, const double*, const float*, int, int); \
   template void gather19<S>(lbm_ctx*, const lbm::Bufs&, float*);                                                \
   template void scatter19<S>(lbm_ctx*, const lbm::Bufs&, const float*);                                         \
   }

@@ -63,18 +63,22 @@ void init27(lbm_ctx* c, const lbm::q27::Bufs27& b) {
 }
 
 template <class S>
-void gather27(lbm_ctx* c, const lbm::q27::Bufs27& b, float* dst) {
-  with_parity(c->t, [&](auto odd) {
-    hipLaunchKernelGGL((q27::k_gather_state<S, decltype(odd)::value>), dim3(c->nblk), dim3(BLOCK), 0, c->stream,
-                       c->P, b, dst);
+void state_out27(lbm_ctx* c, const lbm::q27::Bufs27& b, double* f, float* omega, int i0, int i1) {
+  with_shift(c->grid.shift_mode, [&](auto shw) {
+    with_parity(c->t, [&](auto odd) {
+      hipLaunchKernelGGL((q27::k_state_out<S, decltype(shw)::value, decltype(odd)::value>), dim3(c->nblk), dim3(BLOCK), 0,
+                         c->stream, c->P, b, (const uint32_t*)(c->ws + c->L.wrank), f, omega, i0, i1, (uint32_t)c->nf);
+    });
   });
 }
 
 template <class S>
-void scatter27(lbm_ctx* c, const lbm::q27::Bufs27& b, const float* src) {
-  with_parity(c->t, [&](auto odd) {
-    hipLaunchKernelGGL((q27::k_scatter_state<S, decltype(odd)::value>), dim3(c->nblk), dim3(BLOCK), 0, c->stream,
-                       c->P, b, src);
+void state_in27(lbm_ctx* c, const lbm::q27::Bufs27& b, const double* f, const float* omega, int i0, int i1) {
+  with_shift(c->grid.shift_mode, [&](auto shw) {
+    with_parity(c->t, [&](auto odd) {
+      hipLaunchKernelGGL((q27::k_state_in<S, decltype(shw)::value, decltype(odd)::value>), dim3(c->nblk), dim3(BLOCK), 0,
+                         c->stream, c->P, b, (const uint32_t*)(c->ws + c->L.wrank), f, omega, i0, i1, (uint32_t)c->nf);
+    });
   });
 }
 
@@ -86,6 +90,6 @@ void scatter27(lbm_ctx* c, const lbm::q27::Bufs27& b, const float* src) {
   template void moments27<S>(lbm_ctx*, const lbm::q27::Bufs27&, const lbm::Dense&);                               \
   template void diag27<S>(lbm_ctx*, const lbm::q27::Bufs27&);                                                     \
   template void init27<S>(lbm_ctx*, const lbm::q27::Bufs27&);                                                     \
-  template void gather27<S>(lbm_ctx*, const lbm::q27::Bufs27&, float*);                                           \
-  template void scatter27<S>(lbm_ctx*, const lbm::q27::Bufs27&, const float*);                                    \
+  template void state_out27<S>(lbm_ctx*, const lbm::q27::Bufs27&, double*, float*, int, int); \
+  template void state_in27<S>(lbm_ctx*, const lbm::q27::Bufs27&, const double*, const float*, int, int); \
   }

@@ -17,6 +17,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -120,6 +121,7 @@ Layout make_layout(const lbm_grid& g, int64_t nc, int64_t nrow, int T, int ckpt)
   L.omega = take((size_t)nc * 4);
   L.delta = take((size_t)nrow * 8 * 4);
   L.rel = take((size_t)nrow * 8 * 4);
+  L.wrank = take((size_t)wave_records(nc) * 4);
   L.winfo = take((size_t)wave_records(nc) * sizeof(lbm::WaveInfo));
   L.shape = take((size_t)nrow * 4);
   L.rowbox = take((size_t)nrow * 4);
@@ -237,12 +239,10 @@ lbm_status check_phi(const lbm_ctx* c, const float* phi) {
 // Upload the porosity and the link words (which depend on it).
 lbm_status upload_phi(lbm_ctx* c, const float* phi) {
   std::vector<float> box(c->nbox, 0.0f), comp(c->nc, 0.0f);
-  c->phi_f.resize(c->nf);
   for (int64_t k = 0; k < c->nf; ++k) {
     const float v = phi[c->fluid_box[k]];
     box[c->fluid_box[k]] = v;
     comp[c->fluid_c[k]] = v;
-    c->phi_f[k] = v;
   }
   std::vector<uint32_t> links;
   std::vector<uint64_t> links64;
@@ -317,8 +317,7 @@ lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t 
 lbm_status gather_state(lbm_ctx* c, float* dst) {
   with_storage(c->grid.storage, [&](auto tag) {
     using S = typename decltype(tag)::T;
-    if (c->q == 27) gather27<S>(c, bufs27(c), dst);
-    else gather19<S>(c, bufs(c), dst);
+    gather19<S>(c, bufs(c), dst);
   });
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;
@@ -328,8 +327,7 @@ lbm_status gather_state(lbm_ctx* c, float* dst) {
 lbm_status scatter_state(lbm_ctx* c, const float* src) {
   with_storage(c->grid.storage, [&](auto tag) {
     using S = typename decltype(tag)::T;
-    if (c->q == 27) scatter27<S>(c, bufs27(c), src);
-    else scatter19<S>(c, bufs(c), src);
+    scatter19<S>(c, bufs(c), src);
   });
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;
@@ -418,21 +416,50 @@ lbm_status diag_launch(lbm_ctx* c, double* part = nullptr) {
   return LBM_OK;
 }
 
-// The host copy of the porosity per fluid cell (for the state transfer's rest
-// values), refreshed from the device after lbm_set_porosity.
-lbm_status refresh_phi_host(lbm_ctx* c) {
-  if (!c->phi_stale) return LBM_OK;
-  std::vector<float> comp(c->nc);
-  HIP_TRY(c, hipMemcpyAsync(comp.data(), c->ws + c->L.phi, comp.size() * 4, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  for (int64_t k = 0; k < c->nf; ++k) c->phi_f[k] = comp[c->fluid_c[k]];
-  c->phi_stale = false;
-  return LBM_OK;
+// The state in fluid order through the stage area, as many directions at a time
+// as it holds in FP64 (at least half of them: it has room for q + 1 planes of
+// FP32).  What bounds it: the host link and the clearing of the caller's fresh
+// pages.  The conversion to and from populations runs on the device (45 MB, 296 748
+// cells D3Q19: lbm_get_state 7.2 -> 4.6 ms and with touch_pages 3.4 ms,
+// lbm_set_state 4.2 -> 1.6 ms, against a conversion by a host loop).
+int stage_directions(const lbm_ctx* c) {
+  return (int)std::min<size_t>((size_t)c->q, (size_t)(c->q + 1) * (size_t)c->nc * 4 / ((size_t)c->nf * 8));
 }
 
-double rest_value(const lbm_ctx* c, int i, int64_t k) {
-  const double w = c->q == 27 ? q27::kw(i) / 216.0 : (i == 0 ? 1.0 / 3.0 : (i < 7 ? 1.0 / 18.0 : 1.0 / 36.0));
-  return w * (c->grid.shift_mode ? 1.0 : c->phi_f[k]);
+// Touch the pages of a caller's output buffer from a few threads, before the copy
+// into it: fresh pages are cleared by the kernel at their first use, which one
+// thread does at about 10 GB/s (and the copy engine's copy would wait for it).
+void touch_pages(void* at, size_t bytes) {
+  constexpr size_t PAGE = 4096, MIN_PER_THREAD = size_t(4) << 20;
+  const size_t n = std::min<size_t>(bytes / MIN_PER_THREAD, 8);
+  if (n < 2) return;
+  auto touch = [&](size_t b, size_t e) {
+    for (size_t o = b; o < e; o += PAGE) *((volatile char*)at + o) = 0;
+  };
+  const size_t run = (bytes / n + PAGE - 1) / PAGE * PAGE;
+  std::vector<std::thread> others;
+  try {
+    for (size_t k = 1; k < n; ++k) others.emplace_back(touch, std::min(bytes, k * run), std::min(bytes, (k + 1) * run));
+  } catch (...) {
+    // no thread to be had: the copy touches the rest of the pages itself
+  }
+  touch(0, run);
+  for (std::thread& t : others) t.join();
+}
+
+void state_out(lbm_ctx* c, double* f, float* omega, int i0, int i1) {
+  with_storage(c->grid.storage, [&](auto tag) {
+    using S = typename decltype(tag)::T;
+    if (c->q == 27) state_out27<S>(c, bufs27(c), f, omega, i0, i1);
+    else state_out19<S>(c, bufs(c), f, omega, i0, i1);
+  });
+}
+void state_in(lbm_ctx* c, const double* f, const float* omega, int i0, int i1) {
+  with_storage(c->grid.storage, [&](auto tag) {
+    using S = typename decltype(tag)::T;
+    if (c->q == 27) state_in27<S>(c, bufs27(c), f, omega, i0, i1);
+    else state_in19<S>(c, bufs(c), f, omega, i0, i1);
+  });
 }
 
 }  // namespace
@@ -592,6 +619,11 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* solid, const float* p
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.delta, c->delta.data(), c->delta.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.rel, c->rel.data(), c->rel.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.shape, shape.data(), shape.size() * 4, hipMemcpyHostToDevice, c->stream));
+  std::vector<uint32_t> wrank((size_t)wave_records(c->nc), 0u);  // fluid cells before each wave of 64 compact cells
+  for (const int64_t ci : c->fluid_c)
+    if ((size_t)(ci >> 6) + 1 < wrank.size()) wrank[(ci >> 6) + 1] += 1;
+  for (size_t w = 1; w < wrank.size(); ++w) wrank[w] += wrank[w - 1];
+  HIP_TRY0(hipMemcpyAsync(c->ws + c->L.wrank, wrank.data(), wrank.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.lines, c->lines.data(), c->lines.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.rowbox, c->rowbox.data(), c->rowbox.size() * 4, hipMemcpyHostToDevice, c->stream));
   if (P.in_table > 0)
@@ -706,61 +738,43 @@ lbm_status lbm_diagnostics_noalloc(lbm_ctx* c, double* out) {
 lbm_status lbm_get_state(lbm_ctx* c, double* f, float* omega) {
   CTX_CHECK(c);
   if (!f && !omega) return fail(LBM_E_INVALID, "nothing to get");
-  if (f) {
-    lbm_status s = refresh_phi_host(c);
-    if (s != LBM_OK) return s;
-  }
-  float* stage = (float*)(c->ws + c->L.stage);
-  const size_t nf = (size_t)c->nf, nc = (size_t)c->nc;
-  if (f) {
-    lbm_status s = gather_state(c, stage);
-    if (s != LBM_OK) return s;
-    const int q = c->q;
-    std::vector<float> h(q * nc);
-    HIP_TRY(c, hipMemcpyAsync(h.data(), stage, h.size() * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    const double iU = 1.0 / c->U;
-    for (int i = 0; i < q; ++i)
-      for (size_t k = 0; k < nf; ++k) {
-        const float v = h[i * nc + c->fluid_c[k]];
-        f[i * nf + k] = std::isnan(v) ? 0.0 : (double)v * iU + rest_value(c, i, (int64_t)k);
-      }
+  void* stage = c->ws + c->L.stage;
+  const size_t nf = (size_t)c->nf;
+  const int nd = stage_directions(c);
+  for (int i0 = 0; f && i0 < c->q; i0 += nd) {
+    const int i1 = std::min(c->q, i0 + nd);
+    state_out(c, (double*)stage, nullptr, i0, i1);
+    HIP_TRY(c, hipGetLastError());
+    if (i0 == 0) touch_pages(f, (size_t)c->q * nf * 8);
+    HIP_TRY(c, hipMemcpyAsync(f + (size_t)i0 * nf, stage, (size_t)(i1 - i0) * nf * 8, hipMemcpyDeviceToHost, c->stream));
   }
   if (omega) {
-    std::vector<float> h(nc);
-    HIP_TRY(c, hipMemcpyAsync(h.data(), c->ws + c->L.omega, nc * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    for (size_t k = 0; k < nf; ++k) omega[k] = h[c->fluid_c[k]];
+    state_out(c, nullptr, (float*)stage, 0, 0);
+    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, hipMemcpyAsync(omega, stage, nf * 4, hipMemcpyDeviceToHost, c->stream));
   }
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
   return LBM_OK;
 }
 
 lbm_status lbm_set_state(lbm_ctx* c, const double* f, const float* omega) {
   CTX_CHECK(c);
   if (!f && !omega) return fail(LBM_E_INVALID, "nothing to set");
-  if (f) {
-    lbm_status s = refresh_phi_host(c);
-    if (s != LBM_OK) return s;
-  }
-  float* stage = (float*)(c->ws + c->L.stage);
-  const size_t nf = (size_t)c->nf, nc = (size_t)c->nc;
-  if (f) {
-    const int q = c->q;
-    std::vector<float> h(q * nc, 0.0f);
-    for (int i = 0; i < q; ++i)
-      for (size_t k = 0; k < nf; ++k)
-        h[i * nc + c->fluid_c[k]] = (float)((f[i * nf + k] - rest_value(c, i, (int64_t)k)) * c->U);
-    HIP_TRY(c, hipMemcpyAsync(stage, h.data(), h.size() * 4, hipMemcpyHostToDevice, c->stream));
-    lbm_status s = scatter_state(c, stage);
-    if (s != LBM_OK) return s;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+  void* stage = c->ws + c->L.stage;
+  const size_t nf = (size_t)c->nf;
+  const int nd = stage_directions(c);
+  for (int i0 = 0; f && i0 < c->q; i0 += nd) {
+    const int i1 = std::min(c->q, i0 + nd);
+    HIP_TRY(c, hipMemcpyAsync(stage, f + (size_t)i0 * nf, (size_t)(i1 - i0) * nf * 8, hipMemcpyHostToDevice, c->stream));
+    state_in(c, (const double*)stage, nullptr, i0, i1);
+    HIP_TRY(c, hipGetLastError());
   }
   if (omega) {
-    std::vector<float> h(nc, 0.0f);
-    for (size_t k = 0; k < nf; ++k) h[c->fluid_c[k]] = omega[k];
-    HIP_TRY(c, hipMemcpyAsync(c->ws + c->L.omega, h.data(), nc * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, hipMemcpyAsync(stage, omega, nf * 4, hipMemcpyHostToDevice, c->stream));
+    state_in(c, nullptr, (const float*)stage, 0, 0);
+    HIP_TRY(c, hipGetLastError());
   }
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
   return LBM_OK;
 }
 
@@ -781,7 +795,6 @@ lbm_status lbm_set_porosity(lbm_ctx* c, const float* phi) {
     return fail(LBM_E_INVALID, "porosity must lie in (0, 1] on every fluid cell and be 1 on open-face cells "
                                "(box index " + std::to_string(box) + ")");
   }
-  c->phi_stale = true;
   return launch_init(c);
 }
 

@@ -39,7 +39,7 @@ constexpr size_t INFINITY_CACHE_BYTES = (size_t)256 << 20;
 inline int step_nt(int storage) { return storage == LBM_STORE_FP32 ? 256 : STEP_NT16; }
 
 struct Layout {
-  size_t A, code, links, phi, omega, delta, rel, winfo, shape, rowbox, lines, stage, part, diag, obj, tc, wave, side;
+  size_t A, code, links, phi, omega, delta, rel, winfo, wrank, shape, rowbox, lines, stage, part, diag, obj, tc, wave, side;
   // adjoint
   size_t ck, rec, rho, ah, omh, phih, aside;
   int nck, ckpt, T;
@@ -63,8 +63,6 @@ struct lbm_ctx : lbmrt::HostLayout {
   int q = 19;                     // velocity set
   double U = 36.0;
   int device = 0;                 // HIP device of the workspace (current at lbm_create)
-  std::vector<double> phi_f;      // porosity per fluid cell (host, for state transfer)
-  bool phi_stale = false;         // phi_f predates a device-side porosity update
   hipStream_t stream = nullptr;
   char* ws = nullptr;
   size_t ws_bytes = 0;
@@ -148,14 +146,19 @@ template <class S> void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, bool re
 template <class S> void moments19(lbm_ctx* c, const lbm::Bufs& b, const lbm::Dense& out);
 template <class S> void diag19(lbm_ctx* c, const lbm::Bufs& b);
 template <class S> void init19(lbm_ctx* c, const lbm::Bufs& b);
+// FP64 populations of directions [i0, i1) and omega (null: neither read nor
+// written) in fluid order, device to device.
+template <class S> void state_out19(lbm_ctx* c, const lbm::Bufs& b, double* f, float* omega, int i0, int i1);
+template <class S> void state_in19(lbm_ctx* c, const lbm::Bufs& b, const double* f, const float* omega, int i0, int i1);
 template <class S> void gather19(lbm_ctx* c, const lbm::Bufs& b, float* dst);
 template <class S> void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src);
 template <class S> void step27(lbm_ctx* c, const lbm::q27::Bufs27& b, int diag);
 template <class S> void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, const lbm::Dense& out);
 template <class S> void diag27(lbm_ctx* c, const lbm::q27::Bufs27& b);
 template <class S> void init27(lbm_ctx* c, const lbm::q27::Bufs27& b);
-template <class S> void gather27(lbm_ctx* c, const lbm::q27::Bufs27& b, float* dst);
-template <class S> void scatter27(lbm_ctx* c, const lbm::q27::Bufs27& b, const float* src);
+template <class S> void state_out27(lbm_ctx* c, const lbm::q27::Bufs27& b, double* f, float* omega, int i0, int i1);
+template <class S> void state_in27(lbm_ctx* c, const lbm::q27::Bufs27& b, const double* f, const float* omega, int i0,
+                                   int i1);
 
 // Workgroups of k_moments outside the rows.
 inline unsigned dense_blocks(const lbm::Dense& out) {

@@ -1362,10 +1362,97 @@ __device__ __forceinline__ bool kept_unknown(const Params& p, uint32_t lk) {
   return CX[I] == -1 && (lk & LK_OUT) && p.outlet == 2;
 }
 
-// State out: the pulled (pre-collision) stored values as FP32, [19][nc]; the
-// host converts them back to populations in FP64.  Open-face unknowns are NaN,
-// except the extrapolation outflow's, which are part of the state: their
-// value at time t is extrapolated as the next step would.
+// The fluid index of a cell (ascending box order, which is the compact order
+// without the dead slots) from the count of fluid cells before its wave; every
+// lane of the wave takes part.
+__device__ __forceinline__ uint32_t fluid_rank(const uint32_t* __restrict__ wrank, uint32_t c, bool fluid) {
+  const uint64_t m = __ballot(fluid);
+  const uint32_t lane = threadIdx.x & 63u;
+  return wrank[__builtin_amdgcn_readfirstlane(c >> 6)] + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+}
+// Population rest value of direction weight w at a cell, in FP64.
+template <bool SHW>
+__device__ __forceinline__ double rest_value(double w, float phi) {
+  return SHW ? w : w * (double)phi;
+}
+
+// State out: directions [i0, i1) as FP64 populations in fluid order, out[i - i0][nf],
+// exactly as the stored values convert: v / U plus the rest value, the product
+// and the sum rounded each (no contraction).  Open-face unknowns are 0, except
+// the extrapolation outflow's, which are part of the state: their value at time
+// t is extrapolated as the next step would.  omega (null: not asked for) is the
+// relaxation rate in fluid order.
+template <class S, bool SHW, bool ODD>
+__global__ __launch_bounds__(BLOCK) void k_state_out(Params p, Bufs b, const uint32_t* wrank, double* out, float* omega,
+                                                     int i0, int i1, uint32_t nf) {
+#pragma clang fp contract(off)
+  const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
+  const uint32_t lk = c < (uint32_t)p.nc ? b.links[c] : LK_DEAD;
+  const bool fluid = !(lk & LK_DEAD);
+  const uint32_t k = fluid_rank(wrank, c, fluid);
+  if (!fluid) return;
+  if (omega) omega[k] = b.omega[c];
+  Pos q = position(p, c, b.code[c]);
+  if (ODD) load_deltas(b.delta, q);
+  const Pop<S> A(b.A, p.abytes);
+  const float phi = ldo(b.phi, c);
+  float d[Q];
+  sfor<0, Q>([&](auto ic) {
+    constexpr int I = decltype(ic)::value;
+    if (I < i0 || I >= i1) return;
+    const Slot a = slot_in<I, ODD, S>(p, c, lk, q);
+    d[I] = A.ld(a.v, a.s);
+  });
+  if ((lk & LK_OUT) && p.outlet == 2) extrapolate_out(q.row, lk, b.side + (ODD ? (size_t)p.nrow * 10 : 0), d);
+  sfor<0, Q>([&](auto ic) {
+    constexpr int I = decltype(ic)::value;
+    if (I < i0 || I >= i1) return;
+    const bool none = (open_unknown<I>(lk) && !kept_unknown<I>(p, lk)) || __builtin_isnan(d[I]);
+    const double v = (double)d[I] * p.d.iU;
+    const double f = v + rest_value<SHW>(I == 0 ? 1.0 / 3.0 : (I < 7 ? 1.0 / 18.0 : 1.0 / 36.0), phi);
+    out[(size_t)(I - i0) * nf + k] = none ? 0.0 : f;
+  });
+}
+
+// State in: inverse of k_state_out; each slot that some consumer reads is written
+// exactly once (by that consumer's link).  A kept unknown of the extrapolation
+// outflow goes to both side values, so that the next step's extrapolation
+// returns it.
+template <class S, bool SHW, bool ODD>
+__global__ __launch_bounds__(BLOCK) void k_state_in(Params p, Bufs b, const uint32_t* wrank, const double* in,
+                                                    const float* omega, int i0, int i1, uint32_t nf) {
+#pragma clang fp contract(off)
+  const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
+  const uint32_t lk = c < (uint32_t)p.nc ? b.links[c] : LK_DEAD;
+  const bool fluid = !(lk & LK_DEAD);
+  const uint32_t k = fluid_rank(wrank, c, fluid);
+  if (!fluid) return;
+  if (omega) b.omega[c] = omega[k];
+  Pos q = position(p, c, b.code[c]);
+  if (ODD) load_deltas(b.delta, q);
+  const Pop<S> A(b.A, p.abytes);
+  const float phi = ldo(b.phi, c);
+  sfor<0, Q>([&](auto ic) {
+    constexpr int I = decltype(ic)::value;
+    if (I < i0 || I >= i1) return;
+    const Slot a = slot_in<I, ODD, S>(p, c, lk, q);
+    const double f = in[(size_t)(I - i0) * nf + k] - rest_value<SHW>(I == 0 ? 1.0 / 3.0 : (I < 7 ? 1.0 / 18.0 : 1.0 / 36.0), phi);
+    const float v = (float)(f * p.d.U);
+    if (kept_unknown<I>(p, lk) && open_unknown<I>(lk)) {
+      int j = 0;
+#pragma unroll
+      for (int n = 0; n < 5; ++n) j = XOUT[n] == I ? n : j;
+      float* e = b.side + (ODD ? (size_t)p.nrow * 10 : 0) + (size_t)q.row * 10;
+      e[j] = v;
+      e[5 + j] = v;
+    } else if (!open_unknown<I>(lk)) {
+      A.st(a.v, a.s, v);
+    }
+  });
+}
+
+// The state between two steps for the adjoint's checkpoints: the pulled
+// (pre-collision) stored values as FP32, [19][nc].
 template <class S, bool ODD>
 __global__ __launch_bounds__(BLOCK) void k_gather_state(Params p, Bufs b, float* out) {
   const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
@@ -1389,10 +1476,6 @@ __global__ __launch_bounds__(BLOCK) void k_gather_state(Params p, Bufs b, float*
   });
 }
 
-// State in: inverse of k_gather_state; each slot that some consumer reads is
-// written exactly once (by that consumer's link).  A kept unknown of the
-// extrapolation outflow goes to both side values, so that the next step's
-// extrapolation returns it.
 template <class S, bool ODD>
 __global__ __launch_bounds__(BLOCK) void k_scatter_state(Params p, Bufs b, const float* in) {
   const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;

@@ -519,18 +519,24 @@ __device__ __forceinline__ bool kept_unknown(const Params& p, uint64_t lk) {
 }
 
 // State out / in, as in step.hpp.
-template <class S, bool ODD>
-__global__ __launch_bounds__(BLOCK) void k_gather_state(Params p, Bufs27 b, float* out) {
+template <class S, bool SHW, bool ODD>
+__global__ __launch_bounds__(BLOCK) void k_state_out(Params p, Bufs27 b, const uint32_t* wrank, double* out, float* omega,
+                                                     int i0, int i1, uint32_t nf) {
+#pragma clang fp contract(off)
   const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
-  if (c >= (uint32_t)p.nc) return;
-  const uint64_t lk = b.links[c];
-  if (lk & L_DEAD) return;
+  const uint64_t lk = c < (uint32_t)p.nc ? b.links[c] : L_DEAD;
+  const bool fluid = !(lk & L_DEAD);
+  const uint32_t k = fluid_rank(wrank, c, fluid);
+  if (!fluid) return;
+  if (omega) omega[k] = b.omega[c];
   Pos q = position(p, c, b.code[c]);
   if (ODD) load_deltas(b.delta, q);
   const Pop<S> A(b.A, p.abytes);
+  const float phi = ldo(b.phi, c);
   float d[Q];
   sfor<0, Q>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
+    if (I < i0 || I >= i1) return;
     const Slot a = slot_in<I, ODD, S>(p, c, lk, q);
     d[I] = A.ld(a.v, a.s);
   });
@@ -538,34 +544,44 @@ __global__ __launch_bounds__(BLOCK) void k_gather_state(Params p, Bufs27 b, floa
     const float* e = b.side + (ODD ? (size_t)p.nrow * 18 : 0) + (size_t)q.row * 18;
     const bool up = !((lk >> 1) & 1u);
 #pragma unroll
-    for (int k = 0; k < NX; ++k)
-      if ((lk >> (L_UNK + k)) & 1u) d[XOUT[k]] = up ? rfma(CS, e[NX + k] - e[k], e[k]) : e[k];
+    for (int n = 0; n < NX; ++n)
+      if ((lk >> (L_UNK + n)) & 1u) d[XOUT[n]] = up ? rfma(CS, e[NX + n] - e[n], e[n]) : e[n];
   }
   sfor<0, Q>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
-    const bool unk = open_unknown<I>(lk) && !kept_unknown<I>(p, lk);
-    out[(size_t)I * p.nc + c] = unk ? __builtin_nanf("") : d[I];
+    if (I < i0 || I >= i1) return;
+    const bool none = (open_unknown<I>(lk) && !kept_unknown<I>(p, lk)) || __builtin_isnan(d[I]);
+    const double v = (double)d[I] * p.d.iU;
+    const double f = v + rest_value<SHW>(kw(I) / 216.0, phi);
+    out[(size_t)(I - i0) * nf + k] = none ? 0.0 : f;
   });
 }
 
-template <class S, bool ODD>
-__global__ __launch_bounds__(BLOCK) void k_scatter_state(Params p, Bufs27 b, const float* in) {
+template <class S, bool SHW, bool ODD>
+__global__ __launch_bounds__(BLOCK) void k_state_in(Params p, Bufs27 b, const uint32_t* wrank, const double* in,
+                                                    const float* omega, int i0, int i1, uint32_t nf) {
+#pragma clang fp contract(off)
   const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
-  if (c >= (uint32_t)p.nc) return;
-  const uint64_t lk = b.links[c];
-  if (lk & L_DEAD) return;
+  const uint64_t lk = c < (uint32_t)p.nc ? b.links[c] : L_DEAD;
+  const bool fluid = !(lk & L_DEAD);
+  const uint32_t k = fluid_rank(wrank, c, fluid);
+  if (!fluid) return;
+  if (omega) b.omega[c] = omega[k];
   Pos q = position(p, c, b.code[c]);
   if (ODD) load_deltas(b.delta, q);
   const Pop<S> A(b.A, p.abytes);
+  const float phi = ldo(b.phi, c);
   sfor<0, Q>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
+    if (I < i0 || I >= i1) return;
     const Slot a = slot_in<I, ODD, S>(p, c, lk, q);
-    const float v = in[(size_t)I * p.nc + c];
+    const double f = in[(size_t)(I - i0) * nf + k] - rest_value<SHW>(kw(I) / 216.0, phi);
+    const float v = (float)(f * p.d.U);
     if (kept_unknown<I>(p, lk) && open_unknown<I>(lk)) {
-      const int k = unk_index<I>(lk);
+      const int j = unk_index<I>(lk);
       float* e = b.side + (ODD ? (size_t)p.nrow * 18 : 0) + (size_t)q.row * 18;
-      e[k] = v;
-      e[NX + k] = v;
+      e[j] = v;
+      e[NX + j] = v;
     } else if (!open_unknown<I>(lk)) {
       A.st(a.v, a.s, v);
     }
