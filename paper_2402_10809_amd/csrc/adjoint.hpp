@@ -439,7 +439,8 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
     vhx = 0.0; vhy = 0.0; vhz = 0.0;
     // only two contractions of the adjoints of A and B are needed:
     // aM = sum_m Xh_m : M^-1 and bM = sum_m n_m Xh_m : M^-1/2
-    R aM = 0.0, bM = 0.0, n = norm_of(p.an_iters - 1);
+    // (the iterates of a wave of pure fluid are all v, and none was kept)
+    R aM = 0.0, bM = 0.0, n = __all(phx == 1.0) ? rsqrt_(vx * vx + vy * vy + vz * vz) : norm_of(p.an_iters - 1);
     Adj X = inverse(n);
     for (int m = p.an_iters - 1; m >= 0; --m) {
       R wx, wy, wz;
@@ -457,6 +458,12 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
       bM += n * xh;
       // d/dn of X = n B, contracted with Xh, then through n = |u_m|
       const R g = n > 0.0 ? hb * xh * fast_rcp(n) : 0.0;
+      // nothing further back depends on u_m: every remaining term is zero (pure
+      // fluid, whose B is zero, leaves after its last iterate)
+      if (__all(g == 0.0)) {
+        ubx = 0.0; uby = 0.0; ubz = 0.0;
+        break;
+      }
       if (m > 0) {
         n = norm_of(m - 1);
         X = inverse(n);

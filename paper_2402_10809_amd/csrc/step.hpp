@@ -546,7 +546,10 @@ __device__ __forceinline__ void macro_sums(const Params& p, float phx_f, const S
         Bm[k] = hb * kc.Mh[k];
       }
       ux = vx; uy = vy; uz = vz;
-      for (int m = 0; m < p.an_iters; ++m) {
+      // in pure fluid (phi = 1: 1/k = 0) A = Id and B = 0, so every iterate is v
+      // itself; a wave of such cells takes none (a vessel outside its sac)
+      const int iters = __all(phx == one) ? 0 : p.an_iters;
+      for (int m = 0; m < iters; ++m) {
         const R un = rsqrt_(ux * ux + uy * uy + uz * uz);
         iterate(m, un);
         R X[6];
