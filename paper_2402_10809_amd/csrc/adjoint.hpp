@@ -109,8 +109,8 @@ __device__ __forceinline__ const CParams& params_again() {
 // FP64 populations need 60 KB of LDS and the anisotropic medium 20 KB for its
 // iterates, so two workgroups per CU, and get the registers of 2 waves per SIMD.
 template <bool AN, class PH, bool ODD>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(AN || std::is_same<PH, double>::value ? 2 : 3)))
-void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
+__device__ __forceinline__ void adjoint_body(const Params& p, const AdjBufs& a, uint32_t t, float ew, int kind,
+                                             uint32_t block) {
   using R = double;
   constexpr bool P64 = std::is_same<PH, double>::value;  // FP64 adjoint populations
   // The neighbour gathers (adjoint populations of step n+1 and, for the
@@ -127,7 +127,7 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   __shared__ double sn[NIT][BLOCK];
   // FP64 adjoint populations: their high words (the low words go to sq)
   __shared__ float sqh[P64 ? Q : 1][BLOCK];
-  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD) * BLOCK + threadIdx.x;
+  const uint32_t c = block * BLOCK + threadIdx.x;
   if (c >= (uint32_t)p.nc) return;
   uint32_t lk = a.links[c];
   if (lk & LK_DEAD) return;
@@ -618,6 +618,29 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
   }
   const uint64_t ph_lo = __builtin_bit_cast(uint32_t, sh[0][tid]), ph_hi = __builtin_bit_cast(uint32_t, sh[1][tid]);
   a.phih[c] = __builtin_bit_cast(double, ph_lo | (ph_hi << 32)) + phh;
+}
+
+template <bool AN, class PH>
+constexpr int adjoint_waves() { return AN || std::is_same<PH, double>::value ? 2 : 3; }
+
+template <bool AN, class PH, bool ODD>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adjoint_waves<AN, PH>())))
+void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
+  adjoint_body<AN, PH, ODD>(p, a, t, ew, kind, xcd_block(blockIdx.x, gridDim.x, ODD));
+}
+
+// The reverse step of n and a recording step (parity SODD) of the segment before
+// it in one launch, the first nblk workgroups and the others: neither depends on
+// the other.  For grids that leave the chip idle, where either step is bound by
+// the latency of its waves (launch in lbm_adjoint).
+template <bool AN, class PH, bool ODD, bool SODD>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adjoint_waves<AN, PH>())))
+void k_adjoint_and_step(Params p, AdjBufs a, uint32_t t, float ew, int kind, uint32_t nblk, Bufs b) {
+  if (blockIdx.x < nblk)
+    adjoint_body<AN, PH, ODD>(p, a, t, ew, kind, xcd_block(blockIdx.x, nblk, ODD));
+  else
+    step_body<float, false, SODD, 0, 1, double, false, BLOCK, AN, 0, true>(
+        p, b, xcd_block(blockIdx.x - nblk, nblk, SODD) * BLOCK + threadIdx.x, blockIdx.x == nblk);
 }
 
 // Rest state f_i(0, x) = w_i phi(x) on the known links (and on the

@@ -1,5 +1,6 @@
 // lbm_adjoint: the reverse kernel and its checkpointing driver.
 #include <algorithm>
+#include <vector>
 
 #include "adjoint.hpp"
 #include "runtime.hpp"
@@ -8,15 +9,15 @@ using namespace lbmrt;
 
 // Host side of lbm_adjoint: forward pass with checkpoints, then segment-wise
 // recompute (recording pulled values, omega_prev and density) and reverse
-// steps.  The checkpoint of segment s (s >= 1) is the state one step before
-// the segment start, so the recompute also records the density of the step
-// before the segment, which the porosity-jump gather of the segment's first
-// reverse step needs.  Checkpoints hold the gathered (layout-independent)
-// state; the slot layout of a restored state follows the parity of its time.
-// The forward pass records the last segment itself (that segment needs no
-// checkpoint and no recompute); with one segment (ckpt_every >= T) nothing is
-// recomputed.  The recompute reproduces the forward trajectory bit for bit,
-// so the records are the same either way.
+// steps.  The checkpoint of segment s (s >= 1) is the record of the step before
+// the segment's first, made by the forward pass; the recompute starts with that
+// step from the record, which also gives the density of the step before the
+// segment, which the porosity-jump gather of the segment's first reverse step
+// needs.  A record is independent of the slot layout; the slots of a restarted
+// state follow the parity of its time.  The forward pass records the last segment
+// itself (that segment needs no checkpoint and no recompute); with one segment
+// (ckpt_every >= T) nothing is recomputed.  The recompute reproduces the forward
+// trajectory bit for bit, so the records are the same either way.
 extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, int ckpt, double* J,
                                   float* dJ_dphi) {
   CTX_CHECK(c);
@@ -49,58 +50,61 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
   } arith_scope{c, c->amode};
   c->amode = 2;
   const size_t nc = (size_t)c->nc, pl = (size_t)plane_cells(c->nc), nbox = c->nbox;
-  const int nseg = (T + ckpt - 1) / ckpt;
   float* ck = (float*)(c->ws + L.ck);
   float* rec = (float*)(c->ws + L.rec);
   float* rho = (float*)(c->ws + L.rho);
   double* omh = (double*)(c->ws + L.omh);
   double* phih = (double*)(c->ws + L.phih);
   double* objp = (double*)(c->ws + L.obj);
-  auto slot_rec = [&](int k) { return rec + (size_t)k * (Q + 1) * pl; };
-  auto slot_rho = [&](int k) { return rho + (size_t)k * nc; };
-  // checkpoint s: the state at time s * ckpt - 1 (c->t at the call)
-  auto save_ck = [&](int s) -> lbm_status {
-    float* dst = ck + (size_t)s * (Q + 1) * nc;
-    lbm_status st = gather_state(c, dst);
-    if (st != LBM_OK) return st;
-    HIP_TRY(c, hipMemcpyAsync(dst + Q * nc, c->ws + c->L.omega, nc * 4, hipMemcpyDeviceToDevice, c->stream));
-    return LBM_OK;
+  const int nseg = (T + ckpt - 1) / ckpt, s_last = nseg - 1, t0_last = s_last * ckpt;
+  // On grids that leave the chip idle a reverse or a recompute step is bound by
+  // the latency of its waves, so one launch takes a step of each: while segment s
+  // is reversed, segment s - 1 is recomputed. On larger grids both are bound by
+  // memory and take turns (the line between them: TOGETHER_CELLS).
+  const bool together = nseg > 1 && c->nc <= TOGETHER_CELLS;
+  // The record: slots of one step each, given out and taken back one by one, so
+  // that a segment's record grows into the slots that reversing the one after it
+  // has freed (ckpt + 1 slots serve both). held[s & 1][j] is the slot of step j of
+  // segment s; the density of the step before a segment has a place of its own.
+  std::vector<int> free_slots, held[2];
+  if (want_grad) {
+    for (int k = ckpt; k >= 0; --k) free_slots.push_back(k);
+    held[0].assign(ckpt, 0);
+    held[1].assign(ckpt, 0);
+  }
+  auto take_slot = [&](int s, int j) {
+    held[s & 1][j] = free_slots.back();
+    free_slots.pop_back();
   };
-  auto load_ck = [&](int s) -> lbm_status {
-    const float* src = ck + (size_t)s * (Q + 1) * nc;
-    c->t = (int64_t)s * ckpt - 1;
-    launch_set_time(c->stream, (uint32_t*)(c->ws + c->L.tc), (uint32_t)c->t);
-    lbm_status st = scatter_state(c, src);
-    if (st != LBM_OK) return st;
-    HIP_TRY(c, hipMemcpyAsync(c->ws + c->L.omega, src + Q * nc, nc * 4, hipMemcpyDeviceToDevice, c->stream));
-    return LBM_OK;
-  };
+  auto give_slot = [&](int s, int j) { free_slots.push_back(held[s & 1][j]); };
+  auto step_rec = [&](int s, int j) { return rec + (size_t)held[s & 1][j] * (Q + 1) * pl; };
+  auto step_rho = [&](int s, int j) { return rho + (size_t)(j < 0 ? ckpt + 1 + (s & 1) : held[s & 1][j]) * pl; };
+  auto slot_ck = [&](int s) { return ck + (size_t)s * (Q + 1) * pl; };
 
   // forward pass: objective and checkpoints
   lbm_status st = launch_init(c);
   if (st != LBM_OK) return st;
-  HIP_TRY(c, hipMemsetAsync(objp, 0, (size_t)c->sblk * 8, c->stream));
-  const int s_last = nseg - 1, t0_last = s_last * ckpt;
+  const int nwave = blocks_for_nt(c->nc, 64);
+  HIP_TRY(c, hipMemsetAsync(objp, 0, (size_t)nwave * 8, c->stream));
   for (int t = 0; t < T; ++t) {
-    if (want_grad && (t + 1) % ckpt == 0 && (t + 1) / ckpt < s_last) {
-      st = save_ck((t + 1) / ckpt);
-      if (st != LBM_OK) return st;
-    }
     const bool in = t >= obj->t_begin && t < obj->t_end;
     float* r = nullptr;
     float* rr = nullptr;
-    if (want_grad && s_last >= 1 && t == t0_last - 1) {
-      r = slot_rec(0);
-      rr = slot_rho(0);
-    } else if (want_grad && t >= t0_last) {
-      r = slot_rec(t - t0_last + 1);
-      rr = slot_rho(t - t0_last + 1);
+    if (want_grad && t >= t0_last) {
+      take_slot(s_last, t - t0_last);
+      r = step_rec(s_last, t - t0_last);
+      rr = step_rho(s_last, t - t0_last);
+    } else if (want_grad && (t + 1) % ckpt == 0) {
+      // the checkpoint of the segment that starts at t + 1; its density is the
+      // last segment's, or is recorded again from the checkpoint
+      r = slot_ck((t + 1) / ckpt);
+      rr = step_rho(s_last, -1);
     }
     st = launch_step(c, in ? (okind == LBM_OBJ_WSS ? 3 : 2) : 0, r, rr);
     if (st != LBM_OK) return st;
   }
   double jsum = 0.0;
-  st = finalize(c, objp, c->sblk, 1, 0u, &jsum);
+  st = finalize(c, objp, nwave, 1, 0u, &jsum);
   if (st != LBM_OK) return st;
   const double ew = 1.0 / ((double)(obj->t_end - obj->t_begin) * (double)ncount);
   *J = jsum * ew;
@@ -135,41 +139,72 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
   ab.phih = phih;
   ab.ph = ph;
   ab.pl = (uint32_t)pl;
-  for (int s = nseg - 1; s >= 0; --s) {
-    const int t0 = s * ckpt, t1 = std::min(T, t0 + ckpt);
-    if (s < s_last) {
-      if (s == 0) {
-        st = launch_init(c);
-        if (st != LBM_OK) return st;
-      } else {
-        st = load_ck(s);
-        if (st != LBM_OK) return st;
-        st = launch_step(c, 0, slot_rec(0), slot_rho(0));
-        if (st != LBM_OK) return st;
-      }
-      for (int t = t0; t < t1; ++t) {
-        st = launch_step(c, 0, slot_rec(t - t0 + 1), slot_rho(t - t0 + 1));
-        if (st != LBM_OK) return st;
-      }
+  // the start of the recompute of segment s: the rest state, or the step before
+  // the segment from its checkpoint
+  auto restart = [&](int s) -> lbm_status {
+    if (s == 0) return launch_init(c);
+    c->t = (int64_t)s * ckpt - 1;
+    return launch_step(c, 0, slot_ck(s), step_rho(s, -1), true);
+  };
+  // the reverse step of step j of segment s; with `next` also the recording of the
+  // next step of segment s - 1 (at time c->t)
+  auto reverse_step = [&](int s, int j, bool next) -> lbm_status {
+    const int n = s * ckpt + j;
+    ab.rec = step_rec(s, j);
+    ab.rho_prev = step_rho(s, j - 1);
+    ab.aside_in = aside + (size_t)((n + 1) & 1) * c->nrow * 5;
+    ab.aside_out = aside + (size_t)(n & 1) * c->nrow * 5;
+    const float ewn = (n >= obj->t_begin && n < obj->t_end) ? (float)ew : 0.0f;
+    Bufs b = bufs(c);
+    if (next) {
+      const int i = (int)(c->t - (int64_t)(s - 1) * ckpt);
+      take_slot(s - 1, i);
+      b.rec = step_rec(s - 1, i);
+      b.rho_rec = step_rho(s - 1, i);
     }
-    for (int n = t1 - 1; n >= t0; --n) {
-      const int k = n - t0 + 1;
-      ab.rec = slot_rec(k);
-      ab.rho_prev = slot_rho(k - 1);
-      ab.aside_in = aside + (size_t)((n + 1) & 1) * c->nrow * 5;
-      ab.aside_out = aside + (size_t)(n & 1) * c->nrow * 5;
-      const float ewn = (n >= obj->t_begin && n < obj->t_end) ? (float)ew : 0.0f;
-      auto reverse = [&](auto an, auto ph_type, auto odd) {
-        hipLaunchKernelGGL((k_adjoint<decltype(an)::value, decltype(ph_type), decltype(odd)::value>), dim3(c->nblk),
-                           dim3(BLOCK), 0, c->stream, c->P, ab, (uint32_t)n, ewn, okind);
-      };
-      with_parity(n, [&](auto odd) {
-        if (c->P.an_iters > 0 && p64) reverse(std::true_type{}, double{}, odd);
-        else if (c->P.an_iters > 0) reverse(std::true_type{}, float{}, odd);
-        else if (p64) reverse(std::false_type{}, double{}, odd);
-        else reverse(std::false_type{}, float{}, odd);
-      });
-      HIP_TRY(c, hipGetLastError());
+    auto reverse = [&](auto an, auto ph_type, auto odd) {
+      using PH = decltype(ph_type);
+      constexpr bool AN = decltype(an)::value, OD = decltype(odd)::value;
+      if (next)
+        with_parity(c->t, [&](auto sodd) {
+          hipLaunchKernelGGL((k_adjoint_and_step<AN, PH, OD, decltype(sodd)::value>), dim3(2 * c->nblk), dim3(BLOCK),
+                             0, c->stream, c->P, ab, (uint32_t)n, ewn, okind, (uint32_t)c->nblk, b);
+        });
+      else
+        hipLaunchKernelGGL((k_adjoint<AN, PH, OD>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab, (uint32_t)n,
+                           ewn, okind);
+    };
+    with_parity(n, [&](auto odd) {
+      if (c->P.an_iters > 0 && p64) reverse(std::true_type{}, double{}, odd);
+      else if (c->P.an_iters > 0) reverse(std::true_type{}, float{}, odd);
+      else if (p64) reverse(std::false_type{}, double{}, odd);
+      else reverse(std::false_type{}, float{}, odd);
+    });
+    HIP_TRY(c, hipGetLastError());
+    if (next) c->t += 1;
+    give_slot(s, j);
+    return LBM_OK;
+  };
+  for (int s = s_last; s >= 0; --s) {
+    const int nv = std::min(T - s * ckpt, ckpt);
+    if (together && s > 0) {
+      st = restart(s - 1);
+      if (st != LBM_OK) return st;
+    }
+    for (int i = 0; i < nv; ++i) {
+      st = reverse_step(s, nv - 1 - i, together && s > 0);
+      if (st != LBM_OK) return st;
+    }
+    if (s == 0) break;
+    if (!together) {
+      st = restart(s - 1);
+      if (st != LBM_OK) return st;
+    }
+    // the rest of segment s - 1 (all of it where the two take turns)
+    for (int j = (int)(c->t - (int64_t)(s - 1) * ckpt); j < ckpt; ++j) {
+      take_slot(s - 1, j);
+      st = launch_step(c, 0, step_rec(s - 1, j), step_rho(s - 1, j));
+      if (st != LBM_OK) return st;
     }
   }
   HIP_TRY(c, hipMemsetAsync(dJ_dphi, 0, nbox * 4, c->stream));

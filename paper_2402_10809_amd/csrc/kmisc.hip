@@ -1,5 +1,5 @@
 // Kernels without a storage type: the fixed-order reduction of per-block
-// partials, the time-counter set, and the streaming copy of the bandwidth
+// partials, and the streaming copy of the bandwidth
 // reference.
 #include "runtime.hpp"
 
@@ -31,11 +31,6 @@ __global__ __launch_bounds__(FIN_NT) void k_finalize(const double* part, int nbl
     __syncthreads();
   }
   if (threadIdx.x == 0) out[k] = sh[0];
-}
-
-// Set the time counter slot of parity t & 1 to t (one work-item).
-__global__ void k_set_time(uint32_t* tc, uint32_t t) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) tc[t & 1u] = t;
 }
 
 // Plain streaming copy (16-byte vectors), the achievable-bandwidth reference.
@@ -188,10 +183,6 @@ namespace lbmrt {
 void launch_finalize(hipStream_t s, const double* part, int nparts, int n, uint32_t ops, double* out) {
   static_assert(NDIAGP <= 16, "two bits of the operation mask per entry");
   hipLaunchKernelGGL(lbm::k_finalize, dim3((unsigned)n), dim3(lbm::FIN_NT), 0, s, part, nparts, n, ops, out);
-}
-
-void launch_set_time(hipStream_t s, uint32_t* tc, uint32_t t) {
-  hipLaunchKernelGGL(lbm::k_set_time, dim3(1), dim3(64), 0, s, tc, t);
 }
 
 void launch_copy(hipStream_t s, const void* src, void* dst, size_t n16, unsigned blocks) {

@@ -6,7 +6,7 @@
 namespace lbmrt {
 
 template <class S>
-void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, bool rec) {
+void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, int rec) {
   constexpr int NT = std::is_same<S, float>::value ? 256 : STEP_NT16;
   const dim3 grid(c->sblk), block(NT);
   with_shift(c->grid.shift_mode, [&](auto shw) {
@@ -27,39 +27,43 @@ void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, bool rec) {
                 // with rounding to nearest, whose step has the fewest VALU
                 // instructions (with stochastic rounding they gain nothing)
                 if (c->beyond_cache || RM == 0)
-                  hipLaunchKernelGGL((k_step<S, SH, OD, 0, false, R, PJ, NT, AN, RM, true>), grid, block, 0,
+                  hipLaunchKernelGGL((k_step<S, SH, OD, 0, 0, R, PJ, NT, AN, RM, true>), grid, block, 0,
                                      c->stream, c->P, b);
                 else
-                  hipLaunchKernelGGL((k_step<S, SH, OD, 0, false, R, PJ, NT, AN, RM, false>), grid, block, 0,
+                  hipLaunchKernelGGL((k_step<S, SH, OD, 0, 0, R, PJ, NT, AN, RM, false>), grid, block, 0,
                                      c->stream, c->P, b);
               } else {
-                hipLaunchKernelGGL((k_step<S, SH, OD, 0, false, R, PJ, NT, AN, RM>), grid, block, 0, c->stream,
+                hipLaunchKernelGGL((k_step<S, SH, OD, 0, 0, R, PJ, NT, AN, RM>), grid, block, 0, c->stream,
                                    c->P, b);
               }
             } else if (diag == 1) {
-              hipLaunchKernelGGL((k_step<S, SH, OD, 1, false, R, PJ, NT, AN, RM>), grid, block, 0, c->stream, c->P,
+              hipLaunchKernelGGL((k_step<S, SH, OD, 1, 0, R, PJ, NT, AN, RM>), grid, block, 0, c->stream, c->P,
                                  b);
             } else if constexpr (std::is_same<S, float>::value) {
               // the adjoint's forms (FP32 storage only)
               if (rec) {
-                // the recording step, with the objective term when the
-                // forward pass records the last segment
-                if constexpr (!SH) {
-                  if (diag == 2)
-                    hipLaunchKernelGGL((k_step<S, false, OD, 2, true, R, PJ, NT, AN>), grid, block, 0, c->stream,
-                                       c->P, b);
+                // the recording step, with the objective term in the forward
+                // pass, and the step from a checkpoint's record (the
+                // adjoint's passes compute in FP64)
+                if constexpr (!SH && std::is_same<R, double>::value) {
+                  if (rec == 2)
+                    hipLaunchKernelGGL((k_step<S, false, OD, 0, 2, R, PJ, NT, AN>), grid, block, 0, c->stream, c->P,
+                                       b);
+                  else if (diag == 2)
+                    hipLaunchKernelGGL((k_step<S, false, OD, 2, 1, R, PJ, NT, AN>), grid, block, 0, c->stream, c->P,
+                                       b);
                   else if (diag == 3)
-                    hipLaunchKernelGGL((k_step<S, false, OD, 3, true, R, PJ, NT, AN>), grid, block, 0, c->stream,
-                                       c->P, b);
+                    hipLaunchKernelGGL((k_step<S, false, OD, 3, 1, R, PJ, NT, AN>), grid, block, 0, c->stream, c->P,
+                                       b);
                   else
-                    hipLaunchKernelGGL((k_step<S, false, OD, 0, true, R, PJ, NT, AN>), grid, block, 0, c->stream,
-                                       c->P, b);
+                    hipLaunchKernelGGL((k_step<S, false, OD, 0, 1, R, PJ, NT, AN>), grid, block, 0, c->stream, c->P,
+                                       b);
                 }
               } else if (diag == 2) {
-                hipLaunchKernelGGL((k_step<S, SH, OD, 2, false, R, PJ, NT, AN>), grid, block, 0, c->stream, c->P,
+                hipLaunchKernelGGL((k_step<S, SH, OD, 2, 0, R, PJ, NT, AN>), grid, block, 0, c->stream, c->P,
                                    b);
               } else {
-                hipLaunchKernelGGL((k_step<S, SH, OD, 3, false, R, PJ, NT, AN>), grid, block, 0, c->stream, c->P,
+                hipLaunchKernelGGL((k_step<S, SH, OD, 3, 0, R, PJ, NT, AN>), grid, block, 0, c->stream, c->P,
                                    b);
               }
             }
@@ -113,22 +117,6 @@ void init19(lbm_ctx* c, const lbm::Bufs& b) {
 }
 
 template <class S>
-void gather19(lbm_ctx* c, const lbm::Bufs& b, float* dst) {
-  with_parity(c->t, [&](auto odd) {
-    hipLaunchKernelGGL((k_gather_state<S, decltype(odd)::value>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, b,
-                       dst);
-  });
-}
-
-template <class S>
-void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src) {
-  with_parity(c->t, [&](auto odd) {
-    hipLaunchKernelGGL((k_scatter_state<S, decltype(odd)::value>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P,
-                       b, src);
-  });
-}
-
-template <class S>
 void state_out19(lbm_ctx* c, const lbm::Bufs& b, double* f, float* omega, int i0, int i1) {
   with_shift(c->grid.shift_mode, [&](auto shw) {
     with_parity(c->t, [&](auto odd) {
@@ -152,12 +140,10 @@ void state_in19(lbm_ctx* c, const lbm::Bufs& b, const double* f, const float* om
 
 #define LBM_INSTANTIATE19(S)                                                                                    \
   namespace lbmrt {                                                                                             \
-  template void step19<S>(lbm_ctx*, const lbm::Bufs&, int, bool);                                               \
+  template void step19<S>(lbm_ctx*, const lbm::Bufs&, int, int);                                                \
   template void moments19<S>(lbm_ctx*, const lbm::Bufs&, const lbm::Dense&);                                    \
   template void diag19<S>(lbm_ctx*, const lbm::Bufs&);                                                          \
   template void init19<S>(lbm_ctx*, const lbm::Bufs&);                                                          \
   template void state_out19<S>(lbm_ctx*, const lbm::Bufs&, double*, float*, int, int); \
   template void state_in19<S>(lbm_ctx*, const lbm::Bufs&, const double*, const float*, int, int); \
-  template void gather19<S>(lbm_ctx*, const lbm::Bufs&, float*);                                                \
-  template void scatter19<S>(lbm_ctx*, const lbm::Bufs&, const float*);                                         \
   }

@@ -138,9 +138,10 @@ Layout make_layout(const lbm_grid& g, int64_t nc, int64_t nrow, int T, int ckpt)
   L.ckpt = ckpt;
   if (T > 0) {
     L.nck = (T + ckpt - 1) / ckpt;
-    L.ck = take((size_t)L.nck * (Q + 1) * nc * 4);
+    L.ck = take((size_t)L.nck * (Q + 1) * plane_cells(nc) * 4);
+    // a segment's steps and one more; the densities also of the steps before two segments
     L.rec = take((size_t)(ckpt + 1) * (Q + 1) * plane_cells(nc) * 4);
-    L.rho = take((size_t)(ckpt + 1) * nc * 4);
+    L.rho = take((size_t)(ckpt + 3) * plane_cells(nc) * 4);
     L.ah = take(Q * (size_t)plane_cells(nc) * 8);  // adjoint populations, in place: room for FP64
     L.omh = take((size_t)nc * 8);
     L.phih = take((size_t)nc * 8);
@@ -282,9 +283,9 @@ lbm_status launch_init(lbm_ctx* c) {
 
 // One step at time t (in place).  diag: 0 none, 1 diagnostics partials, 2
 // region kinetic energy, 3 region wall shear stress, accumulated into the
-// objective partials.  rec: record the step for the adjoint (FP32, shift
-// mode 0 only).
-lbm_status launch_step(lbm_ctx* c, int diag, float* rec, float* rho_rec) {
+// objective partials.  rec: record the step for the adjoint, or step from that
+// record (FP32, shift mode 0 only).
+lbm_status launch_step(lbm_ctx* c, int diag, float* rec, float* rho_rec, bool from) {
   if (c->q == 27) {
     const q27::Bufs27 b = bufs27(c);
     with_storage(c->grid.storage, [&](auto tag) { step27<typename decltype(tag)::T>(c, b, diag); });
@@ -294,8 +295,9 @@ lbm_status launch_step(lbm_ctx* c, int diag, float* rec, float* rho_rec) {
     if (rec) {
       b.rec = rec;
       b.rho_rec = rho_rec;
+      b.t = (uint32_t)c->t;
     }
-    with_storage(c->grid.storage, [&](auto tag) { step19<typename decltype(tag)::T>(c, b, diag, rec != nullptr); });
+    with_storage(c->grid.storage, [&](auto tag) { step19<typename decltype(tag)::T>(c, b, diag, rec ? (from ? 2 : 1) : 0); });
   }
   HIP_TRY(c, hipGetLastError());
   c->t += 1;
@@ -309,27 +311,6 @@ lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t 
   HIP_TRY(c, hipGetLastError());
   HIP_TRY(c, hipMemcpyAsync(host_out, dout, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  return LBM_OK;
-}
-
-// Pulled state of time t (raw stored values as FP32, [19][nc], compact order)
-// into dst (device).
-lbm_status gather_state(lbm_ctx* c, float* dst) {
-  with_storage(c->grid.storage, [&](auto tag) {
-    using S = typename decltype(tag)::T;
-    gather19<S>(c, bufs(c), dst);
-  });
-  HIP_TRY(c, hipGetLastError());
-  return LBM_OK;
-}
-
-// Inverse of gather_state, into the slots of time t's parity.
-lbm_status scatter_state(lbm_ctx* c, const float* src) {
-  with_storage(c->grid.storage, [&](auto tag) {
-    using S = typename decltype(tag)::T;
-    scatter19<S>(c, bufs(c), src);
-  });
-  HIP_TRY(c, hipGetLastError());
   return LBM_OK;
 }
 

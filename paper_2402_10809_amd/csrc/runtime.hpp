@@ -38,6 +38,15 @@ constexpr int STEP_NT16 = 256;  // work-items per workgroup of the 16-bit step k
 constexpr size_t INFINITY_CACHE_BYTES = (size_t)256 << 20;
 inline int step_nt(int storage) { return storage == LBM_STORE_FP32 ? 256 : STEP_NT16; }
 
+// Compact cells up to which lbm_adjoint records a segment in the launches that
+// reverse the one after it (k_adjoint_and_step). Whole call, the two in turn ->
+// together: 11 968 cells 2 235 -> 1 748 us, 37 736 2 932 -> 2 345 us, 118 304 6 005 ->
+// 5 061 us (checkpoints every 16 or 20 steps); 296 748 5 986 -> 5 500 us, 538 068
+// 9 089 -> 8 538 us, 823 756 12 786 -> 12 187 us, 1 308 792 18 728 -> 18 643 us (with the
+// anisotropic medium and FP64 populations 19 396 -> 19 037 and 28 665 -> 32 568 us
+// for the last two), 2 360 212 27 023 -> 31 349 us.
+constexpr int64_t TOGETHER_CELLS = 786432;
+
 struct Layout {
   size_t A, code, links, phi, omega, delta, rel, winfo, wrank, shape, rowbox, lines, stage, part, diag, obj, tc, wave, side;
   // adjoint
@@ -140,9 +149,9 @@ lbm::q27::Bufs27 bufs27(lbm_ctx* c);
 
 // Per-storage launch functions (kernels instantiated in their own units).
 // diag: 0 none, 1 diagnostics partials, 2 region kinetic energy, 3 region
-// wall shear stress, accumulated into the objective partials; rec: record
-// the step for the adjoint (FP32 storage, shift mode 0 only).
-template <class S> void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, bool rec);
+// wall shear stress, accumulated into the objective partials; rec: 1 record
+// the step for the adjoint, 2 step from a record (FP32 storage, shift mode 0 only).
+template <class S> void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, int rec);
 template <class S> void moments19(lbm_ctx* c, const lbm::Bufs& b, const lbm::Dense& out);
 template <class S> void diag19(lbm_ctx* c, const lbm::Bufs& b);
 template <class S> void init19(lbm_ctx* c, const lbm::Bufs& b);
@@ -150,8 +159,6 @@ template <class S> void init19(lbm_ctx* c, const lbm::Bufs& b);
 // written) in fluid order, device to device.
 template <class S> void state_out19(lbm_ctx* c, const lbm::Bufs& b, double* f, float* omega, int i0, int i1);
 template <class S> void state_in19(lbm_ctx* c, const lbm::Bufs& b, const double* f, const float* omega, int i0, int i1);
-template <class S> void gather19(lbm_ctx* c, const lbm::Bufs& b, float* dst);
-template <class S> void scatter19(lbm_ctx* c, const lbm::Bufs& b, const float* src);
 template <class S> void step27(lbm_ctx* c, const lbm::q27::Bufs27& b, int diag);
 template <class S> void moments27(lbm_ctx* c, const lbm::q27::Bufs27& b, const lbm::Dense& out);
 template <class S> void diag27(lbm_ctx* c, const lbm::q27::Bufs27& b);
@@ -180,7 +187,6 @@ void with_storage(int storage, Fn&& fn) {
 
 // Kernels without a storage type (kmisc.hip).
 void launch_finalize(hipStream_t s, const double* part, int nparts, int n, uint32_t ops, double* out);
-void launch_set_time(hipStream_t s, uint32_t* tc, uint32_t t);
 void launch_copy(hipStream_t s, const void* src, void* dst, size_t n16, unsigned blocks);
 void launch_probe(hipStream_t s, int kind, const void* src, void* dst, size_t n16, unsigned blocks);
 lbm_status set_porosity_device(lbm_ctx* c, const float* phib, uint32_t* bad_cell);
@@ -188,11 +194,10 @@ lbm_status launch_wave_info(lbm_ctx* c);
 
 // Runtime operations shared by the ABI functions (lbm.hip).
 lbm_status launch_init(lbm_ctx* c);
-lbm_status launch_step(lbm_ctx* c, int diag, float* rec, float* rho_rec);
+// from: rec holds the record to step from (b.t = c->t) instead of receiving one
+lbm_status launch_step(lbm_ctx* c, int diag, float* rec, float* rho_rec, bool from = false);
 // dev_out: device area of the reduced vector (nullptr: the workspace's)
 lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t ops, double* host_out,
                     double* dev_out = nullptr);
-lbm_status gather_state(lbm_ctx* c, float* dst);
-lbm_status scatter_state(lbm_ctx* c, const float* src);
 
 }  // namespace lbmrt

@@ -133,11 +133,12 @@ struct Bufs {
   const float* shape;     // inflow profile per row
   const uint32_t* rowbox; // box index of (x = 0) of each row
   double* part;           // per-block partials
-  float* rec;             // recompute record: [20][plane cells] (pulled values, omega_prev)
+  float* rec;             // record: [20][plane cells] (pulled values, omega_prev)
   float* rho_rec;         // recompute record: rho per compact cell
   uint32_t* tc;           // time counter: the step at parity k reads tc[k] and writes t + 1 to tc[1 - k]
   const double* wave;     // sampled inflow waveform (in_table entries)
   float* side;            // extrapolation outflow: [2][nrow][10] kept values by parity
+  uint32_t t;             // time of a step from a record
 };
 
 template <int A, int B, class F>
@@ -269,16 +270,18 @@ __device__ __forceinline__ Slot slot_out(const Params& p, uint32_t c, uint32_t l
 // Pull: v_i(x) = f_i(t, x) (the cell's own opposite output across a wall; the
 // open-face unknowns are then replaced by the Zou-He fill).  Unless UNI, also
 // pt[j] = porosity of x + c_j (phi(x) across walls) for the producer side.
-template <class S, bool SHW, bool UNI, bool ODD, bool INR = false>
+// FR: the values come from a record ([19][pl], already filled) instead.
+template <class S, bool SHW, bool UNI, bool ODD, bool INR = false, bool FR = false>
 __device__ __forceinline__ void pull(const Params& p, const Pop<S>& A, const float* __restrict__ phi, uint32_t c,
-                                     uint32_t lk, const Pos& q, float phx, float v[Q], float pt[Q]) {
+                                     uint32_t lk, const Pos& q, float phx, float v[Q], float pt[Q],
+                                     const float* from = nullptr, uint32_t pl = 0u) {
   auto ld = [&](Slot a) { return A.ld(a.v, a.s); };
-  v[0] = ld(slot_in<0, ODD, S, INR>(p, c, lk, q));
+  v[0] = FR ? __builtin_nontemporal_load(from + c) : ld(slot_in<0, ODD, S, INR>(p, c, lk, q));
   pt[0] = phx;
   sfor<1, Q>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
     constexpr int J = OPP[I];
-    v[I] = ld(slot_in<I, ODD, S, INR>(p, c, lk, q));
+    v[I] = FR ? __builtin_nontemporal_load(from + (size_t)I * pl + c) : ld(slot_in<I, ODD, S, INR>(p, c, lk, q));
     if (!UNI) {
       if constexpr (INR) {
         // interior: the source x - c_I is fluid, at (x, row k) shifted by -c_x
@@ -1021,8 +1024,8 @@ __device__ __forceinline__ uint32_t rec_plane(const Params& p) { return p.plb[1]
 
 // Body of the step for one cell (UNI: the whole wave has uniform neighbour
 // porosity; INR: every cell of the wave is interior; RM: rounding of 16-bit
-// storage, see round16).
-template <class S, bool SHW, bool UNI, bool ODD, int DIAG, bool REC, class R, bool PROJ, bool AN, bool INR, int RM,
+// storage, see round16; REC: see k_step).
+template <class S, bool SHW, bool UNI, bool ODD, int DIAG, int REC, class R, bool PROJ, bool AN, bool INR, int RM,
           bool PL = false, bool PF = false>
 __device__ __forceinline__ void step_cell(const Params& p, const Bufs& b, uint32_t c, uint32_t lk, uint32_t t,
                                           float phx, double (&dv)[NDIAGP], float& ke_reg, uint32_t row = 0u) {
@@ -1048,10 +1051,10 @@ __device__ __forceinline__ void step_cell(const Params& p, const Bufs& b, uint32
   }
   float d[Q], pt[Q];
   const Pop<S> A(b.A, p.abytes);
-  pull<S, SHW, UNI, ODD, INR>(p, A, b.phi, c, lk, q, phx, d, pt);
+  pull<S, SHW, UNI, ODD, INR, REC == 2>(p, A, b.phi, c, lk, q, phx, d, pt, b.rec, rec_plane(p));
   const size_t half = (size_t)p.nrow * 10;
-  open_fill(p, q.row, lk, t, b.shape, b.wave, b.side + (ODD ? half : 0), d);
-  if (REC) {
+  if (REC != 2) open_fill(p, q.row, lk, t, b.shape, b.wave, b.side + (ODD ? half : 0), d);
+  if (REC == 1) {
     // the segment record (after the open-face fill, so that it holds the
     // extrapolation outflow's unknowns) is read once, by the reverse step:
     // stream it past the caches
@@ -1059,14 +1062,12 @@ __device__ __forceinline__ void step_cell(const Params& p, const Bufs& b, uint32
     for (int i = 0; i < Q; ++i) __builtin_nontemporal_store(d[i], &b.rec[(size_t)i * rec_plane(p) + c]);
   }
   if (p.outlet == 2 && (lk & (LK_OUT | LK_UPS))) outflow_keep(p, q.row, lk, phx, d, b.side + (ODD ? 0 : half));
-  const float omp = b.omega[c];
+  const float omp = REC == 2 ? __builtin_nontemporal_load(&b.rec[(size_t)Q * rec_plane(p) + c]) : b.omega[c];
   Macro<R> M;
   macro<R, AN, PF>(p, phx, d, omp, M);
   b.omega[c] = (float)M.omega;
-  if (REC) {
-    __builtin_nontemporal_store(omp, &b.rec[(size_t)Q * rec_plane(p) + c]);
-    __builtin_nontemporal_store((float)M.rho, &b.rho_rec[c]);
-  }
+  if (REC == 1) __builtin_nontemporal_store(omp, &b.rec[(size_t)Q * rec_plane(p) + c]);
+  if (REC) __builtin_nontemporal_store((float)M.rho, &b.rho_rec[c]);
   const bool reg = (lk & LK_REG) != 0;
   if (DIAG == 1) diag_terms<R>(p, phx, d, M, lk, true, dv);
   if (DIAG == 2) ke_reg = reg ? (float)((R)0.5 * M.rho * M.uu) : 0.0f;
@@ -1078,11 +1079,11 @@ __device__ __forceinline__ void step_cell(const Params& p, const Bufs& b, uint32
 // Whether the pure-fluid form serves this wave: the plain step (FP32
 // arithmetic, isotropic, no diagnostics or record), no body force, and
 // porosity 1 at every active lane.
-template <int DIAG, bool REC, class R, bool AN>
+template <int DIAG, int REC, class R, bool AN>
 constexpr bool pure_form() {
-  return DIAG == 0 && !REC && !AN && std::is_same<R, float>::value;
+  return DIAG == 0 && REC == 0 && !AN && std::is_same<R, float>::value;
 }
-template <int DIAG, bool REC, class R, bool AN>
+template <int DIAG, int REC, class R, bool AN>
 __device__ __forceinline__ bool pure_wave(const Params& p, bool active, float phx) {
   if constexpr (!pure_form<DIAG, REC, R, AN>()) {
     return false;
@@ -1095,7 +1096,7 @@ __device__ __forceinline__ bool pure_wave(const Params& p, bool active, float ph
 // link word, with the wave-uniform choice of the uniform-porosity and
 // interior forms; returns whether c is a fluid cell.  Every lane of the wave
 // takes part.
-template <class S, bool SHW, bool ODD, int DIAG, bool REC, class R, bool PROJ, bool AN, int RM>
+template <class S, bool SHW, bool ODD, int DIAG, int REC, class R, bool PROJ, bool AN, int RM>
 __device__ __forceinline__ bool step_any(const Params& p, const Bufs& b, uint32_t c, uint32_t t,
                                          double (&dv)[NDIAGP], float& ke_reg) {
   const uint32_t lk = c < (uint32_t)p.nc ? b.links[c] : LK_DEAD;
@@ -1133,8 +1134,12 @@ __device__ __forceinline__ bool step_any(const Params& p, const Bufs& b, uint32_
 // The step at parity ODD (t odd), NT work-items per workgroup.  DIAG: 0 none,
 // 1 diagnostics of the pre-collision state into part[block][NDIAGP], 2 region
 // kinetic energy, 3 region wall shear stress |tau|, accumulated into
-// part[block].  REC: also record the pulled
-// values and omega_prev ([20][nc]) and rho.
+// part[wave of 64 cells].  REC 1: also record the pulled values and omega_prev
+// ([20][plane cells]) and rho; 2: take them from such a record of step b.t instead
+// of the slots (the open faces' unknowns are in it), and record rho: the step from
+// a checkpoint, which needs no slots restored (the separate gather and scatter
+// of a checkpoint took 78 and 97 us on 2.36 M cells; a recording step costs 25 us
+// more than a plain one).
 // ---------------------------------------------------------------------------
 // The 16-bit odd step needs 97 VGPRs as compiled freely (4 waves per SIMD);
 // asked for 5 waves the compiler fits it in 96 without scratch, and the step
@@ -1153,12 +1158,10 @@ __device__ __forceinline__ bool step_any(const Params& p, const Bufs& b, uint32_
 // take them only when the state exceeds the Infinity Cache: on a cache-resident
 // state the record lookup in front of their loads costs more than the bytes it
 // saves).
-template <class S, bool SHW, bool ODD, int DIAG, bool REC, class R, bool PROJ, int NT, bool AN = false, int RM = 0,
-          bool WR = sizeof(S) == 4>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((ODD && sizeof(S) == 2 && DIAG == 0 && !REC) ? 5 : (sizeof(S) == 4 && DIAG == 0 && !REC && std::is_same<R, float>::value && !AN ? 4 : 1))))
-void k_step(Params p, Bufs b) {
-  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD) * NT + threadIdx.x;
-  const uint32_t t = b.tc[ODD ? 1 : 0];
+// One workgroup's part of the step: cell c, first: the workgroup that sets the time.
+template <class S, bool SHW, bool ODD, int DIAG, int REC, class R, bool PROJ, int NT, bool AN, int RM, bool WR>
+__device__ __forceinline__ void step_body(const Params& p, const Bufs& b, uint32_t c, bool first) {
+  const uint32_t t = REC == 2 ? b.t : b.tc[ODD ? 1 : 0];
   double dv[NDIAGP];
   float ke_reg = 0.0f;
   if constexpr (DIAG == 0 && WR) {
@@ -1179,7 +1182,7 @@ void k_step(Params p, Bufs b) {
         else
           step_cell<S, SHW, false, ODD, DIAG, REC, R, PROJ, AN, true, RM, true>(p, b, c, LK_INR, t, phx, dv, ke_reg,
                                                                                 row);
-        if (blockIdx.x == 0 && threadIdx.x == 0) b.tc[ODD ? 0 : 1] = t + 1u;
+        if (first && threadIdx.x == 0) b.tc[ODD ? 0 : 1] = t + 1u;
         return;
       }
     }
@@ -1195,14 +1198,24 @@ void k_step(Params p, Bufs b) {
     block_reduce<NDIAGP, NT>(dv, ops, b.part + (size_t)blockIdx.x * NDIAGP);
   }
   if (DIAG >= 2) {
-    double v[1] = {(double)ke_reg};
-    const int ops[1] = {0};
-    __shared__ double tmp[1];
-    block_reduce<1, NT>(v, ops, tmp);
-    if (threadIdx.x == 0) b.part[blockIdx.x] += tmp[0];
+    // waves without a region cell contribute nothing
+    if (__any(active && ke_reg != 0.0f)) {
+      double v = active ? (double)ke_reg : 0.0;
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+      if ((threadIdx.x & 63u) == 0u) b.part[c >> 6] += v;
+    }
   }
   // the next step (the other parity) reads t + 1 from the other slot
-  if (blockIdx.x == 0 && threadIdx.x == 0) b.tc[ODD ? 0 : 1] = t + 1u;
+  if (first && threadIdx.x == 0) b.tc[ODD ? 0 : 1] = t + 1u;
+}
+
+template <class S, bool SHW, bool ODD, int DIAG, int REC, class R, bool PROJ, int NT, bool AN = false, int RM = 0,
+          bool WR = sizeof(S) == 4>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((ODD && sizeof(S) == 2 && DIAG == 0 && !REC) ? 5 : (sizeof(S) == 4 && DIAG == 0 && !REC && std::is_same<R, float>::value && !AN ? 4 : 1))))
+void k_step(Params p, Bufs b) {
+  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD) * NT + threadIdx.x;
+  step_body<S, SHW, ODD, DIAG, REC, R, PROJ, NT, AN, RM, WR>(p, b, c, blockIdx.x == 0);
 }
 
 // Dense box outputs: the planes of rho, u, shear, omega, sigma and tau (null
@@ -1448,57 +1461,6 @@ __global__ __launch_bounds__(BLOCK) void k_state_in(Params p, Bufs b, const uint
       float* e = b.side + (ODD ? (size_t)p.nrow * 10 : 0) + (size_t)q.row * 10;
       e[j] = v;
       e[5 + j] = v;
-    } else if (!open_unknown<I>(lk)) {
-      A.st(a.v, a.s, v);
-    }
-  });
-}
-
-// The state between two steps for the adjoint's checkpoints: the pulled
-// (pre-collision) stored values as FP32, [19][nc].
-template <class S, bool ODD>
-__global__ __launch_bounds__(BLOCK) void k_gather_state(Params p, Bufs b, float* out) {
-  const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
-  if (c >= (uint32_t)p.nc) return;
-  const uint32_t lk = b.links[c];
-  if (lk & LK_DEAD) return;
-  Pos q = position(p, c, b.code[c]);
-  if (ODD) load_deltas(b.delta, q);
-  const Pop<S> A(b.A, p.abytes);
-  float d[Q];
-  sfor<0, Q>([&](auto ic) {
-    constexpr int I = decltype(ic)::value;
-    const Slot a = slot_in<I, ODD, S>(p, c, lk, q);
-    d[I] = A.ld(a.v, a.s);
-  });
-  if ((lk & LK_OUT) && p.outlet == 2) extrapolate_out(q.row, lk, b.side + (ODD ? (size_t)p.nrow * 10 : 0), d);
-  sfor<0, Q>([&](auto ic) {
-    constexpr int I = decltype(ic)::value;
-    const bool unk = open_unknown<I>(lk) && !kept_unknown<I>(p, lk);
-    out[(size_t)I * p.nc + c] = unk ? __builtin_nanf("") : d[I];
-  });
-}
-
-template <class S, bool ODD>
-__global__ __launch_bounds__(BLOCK) void k_scatter_state(Params p, Bufs b, const float* in) {
-  const uint32_t c = blockIdx.x * BLOCK + threadIdx.x;
-  if (c >= (uint32_t)p.nc) return;
-  const uint32_t lk = b.links[c];
-  if (lk & LK_DEAD) return;
-  Pos q = position(p, c, b.code[c]);
-  if (ODD) load_deltas(b.delta, q);
-  const Pop<S> A(b.A, p.abytes);
-  sfor<0, Q>([&](auto ic) {
-    constexpr int I = decltype(ic)::value;
-    const Slot a = slot_in<I, ODD, S>(p, c, lk, q);
-    const float v = in[(size_t)I * p.nc + c];
-    if (kept_unknown<I>(p, lk) && open_unknown<I>(lk)) {
-      int k = 0;
-#pragma unroll
-      for (int j = 0; j < 5; ++j) k = XOUT[j] == I ? j : k;
-      float* e = b.side + (ODD ? (size_t)p.nrow * 10 : 0) + (size_t)q.row * 10;
-      e[k] = v;
-      e[5 + k] = v;
     } else if (!open_unknown<I>(lk)) {
       A.st(a.v, a.s, v);
     }

@@ -42,3 +42,25 @@ def test_short_reverse_sweeps(kind, T, ckpt, fp64):
     print(f"  J {J:.10e} oracle {J_ref:.10e}; gradient error {err:.3e} of {scale:.3e}, storage {stored:.3e}", flush=True)
     assert abs(J - J_ref) <= 1e-5 * abs(J_ref) + 1e-30
     assert err < 1e-4 * scale + stored
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("kind", ["open", "open_extrap", "periodic"])
+@pytest.mark.parametrize("T", [7, 8, 9, 12])
+def test_segments_recorded_while_the_next_is_reversed(T, kind, fp64):
+    """Segment lengths around T: a last segment of one step, short and full ones,
+    one segment only.  The recorded trajectory is the same in every case, so the
+    gradients are the same bits as with the whole record."""
+    case = tiny_case(kind, seed=5)
+    if kind == "periodic":
+        case.porous = dict(case.porous, g=tuple(50.0 * v for v in case.porous["g"]))
+    else:
+        case.wave = (0.04, 0.5, 20.0)
+    s = Solver.from_case(case, adjoint_T=T, ckpt=T)
+    J, g = s.adjoint(T // 3, T, T, T, fp64=fp64)
+    for ckpt in (1, 2, 3, 4, T - 1, T + 3):
+        print(f"segments {kind} T={T} ckpt={ckpt} fp64={fp64}", flush=True)
+        s2 = Solver.from_case(case, adjoint_T=T, ckpt=ckpt)
+        J2, g2 = s2.adjoint(T // 3, T, T, ckpt, fp64=fp64)
+        assert J2 == J
+        assert np.array_equal(g2.cpu().numpy(), g.cpu().numpy())
