@@ -1152,8 +1152,8 @@ __device__ __forceinline__ bool step_any(const Params& p, const Bufs& b, uint32_
 // from 58.1 to 56.8 us (FP32) and from 36.7 to 35.2 us (FP16), the odd one from
 // 39.6 to 39.1 us (FP16); on the 9.4 M-cell box, whose 870 MB state exceeds the
 // Infinity Cache, from 319.8 / 344.8 to 307.5 / 335.0 us (FP32, even / odd).
-// The D3Q27 FP32 step (302 MB) measured 92.4 -> 98.3 us on its even step and
-// keeps one direction.
+// D3Q27: with 16-bit storage 52.3 -> 51.4 us per step; the FP32 step (302 MB)
+// measured 92.4 -> 98.3 us on its even step and keeps one direction.
 // WR: the wave records are used (always with FP32 storage; the 16-bit steps
 // take them only when the state exceeds the Infinity Cache: on a cache-resident
 // state the record lookup in front of their loads costs more than the bytes it

@@ -421,7 +421,8 @@ __device__ __forceinline__ void step_cell(const Params& p, const Bufs27& b, uint
 // One D3Q27 step at parity ODD.  DIAG: 0 none, 1 diagnostics partials.
 template <class S, bool SHW, bool ODD, int DIAG, class R, bool PROJ, int NT, int RM = 0>
 __global__ __launch_bounds__(NT) void k_step(Params p, Bufs27 b) {
-  const uint32_t c = xcd_block(blockIdx.x, gridDim.x) * NT + threadIdx.x;
+  // backwards on odd steps with 16-bit storage: see step.hpp's k_step
+  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD && sizeof(S) == 2) * NT + threadIdx.x;
   const uint32_t t = b.tc[ODD ? 1 : 0];
   const uint64_t lk = c < (uint32_t)p.nc ? b.links[c] : L_DEAD;
   const bool active = !(lk & L_DEAD);
