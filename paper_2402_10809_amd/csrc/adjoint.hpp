@@ -108,7 +108,7 @@ __device__ __forceinline__ const CParams& params_again() {
 //     recompute (53 248 B per workgroup: three workgroups fit the 160 KiB).
 // FP64 populations need 60 KB of LDS and the anisotropic medium 20 KB for its
 // iterates, so two workgroups per CU, and get the registers of 2 waves per SIMD.
-template <bool AN, class PH, bool ODD>
+template <bool AN, class PH, bool ODD, int NT>
 __device__ __forceinline__ void adjoint_body(const Params& p, const AdjBufs& a, uint32_t t, float ew, int kind,
                                              uint32_t block) {
   using R = double;
@@ -118,16 +118,16 @@ __device__ __forceinline__ void adjoint_body(const Params& p, const AdjBufs& a, 
   // the start, so that their latency overlaps the forward recompute without
   // holding registers.  Each wave reads back only the slots its own loads
   // wrote: no barrier, one wait for the loads.
-  __shared__ float sq[Q][BLOCK], sr[Q - 1][BLOCK], sh[4][BLOCK];
+  __shared__ float sq[Q][NT], sr[Q - 1][NT], sh[4][NT];
   // the last pulled values of the record, across the forward recompute (see above)
   constexpr int SDN = ODD && !P64 && !AN ? 11 : 0;
-  __shared__ float sd[SDN > 0 ? SDN : 1][BLOCK];
+  __shared__ float sd[SDN > 0 ? SDN : 1][NT];
   // anisotropic permeability: |u_m| of the first iterates
   constexpr int NIT = AN ? 10 : 1;
-  __shared__ double sn[NIT][BLOCK];
+  __shared__ double sn[NIT][NT];
   // FP64 adjoint populations: their high words (the low words go to sq)
-  __shared__ float sqh[P64 ? Q : 1][BLOCK];
-  const uint32_t c = block * BLOCK + threadIdx.x;
+  __shared__ float sqh[P64 ? Q : 1][NT];
+  const uint32_t c = block * NT + threadIdx.x;
   if (c >= (uint32_t)p.nc) return;
   uint32_t lk = a.links[c];
   if (lk & LK_DEAD) return;
@@ -623,24 +623,24 @@ __device__ __forceinline__ void adjoint_body(const Params& p, const AdjBufs& a, 
 template <bool AN, class PH>
 constexpr int adjoint_waves() { return AN || std::is_same<PH, double>::value ? 2 : 3; }
 
-template <bool AN, class PH, bool ODD>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adjoint_waves<AN, PH>())))
+template <bool AN, class PH, bool ODD, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(adjoint_waves<AN, PH>())))
 void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
-  adjoint_body<AN, PH, ODD>(p, a, t, ew, kind, xcd_block(blockIdx.x, gridDim.x, ODD));
+  adjoint_body<AN, PH, ODD, NT>(p, a, t, ew, kind, xcd_block(blockIdx.x, gridDim.x, ODD));
 }
 
 // The reverse step of n and a recording step (parity SODD) of the segment before
 // it in one launch, the first nblk workgroups and the others: neither depends on
 // the other.  For grids that leave the chip idle, where either step is bound by
 // the latency of its waves (launch in lbm_adjoint).
-template <bool AN, class PH, bool ODD, bool SODD>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adjoint_waves<AN, PH>())))
+template <bool AN, class PH, bool ODD, bool SODD, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(adjoint_waves<AN, PH>())))
 void k_adjoint_and_step(Params p, AdjBufs a, uint32_t t, float ew, int kind, uint32_t nblk, Bufs b) {
   if (blockIdx.x < nblk)
-    adjoint_body<AN, PH, ODD>(p, a, t, ew, kind, xcd_block(blockIdx.x, nblk, ODD));
+    adjoint_body<AN, PH, ODD, NT>(p, a, t, ew, kind, xcd_block(blockIdx.x, nblk, ODD));
   else
-    step_body<float, false, SODD, 0, 1, double, false, BLOCK, AN, 0, true>(
-        p, b, xcd_block(blockIdx.x - nblk, nblk, SODD) * BLOCK + threadIdx.x, blockIdx.x == nblk);
+    step_body<float, false, SODD, 0, 1, double, false, NT, AN, 0, true>(
+        p, b, xcd_block(blockIdx.x - nblk, nblk, SODD) * NT + threadIdx.x, blockIdx.x == nblk);
 }
 
 // Rest state f_i(0, x) = w_i phi(x) on the known links (and on the

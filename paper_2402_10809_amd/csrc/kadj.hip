@@ -146,6 +146,10 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
     c->t = (int64_t)s * ckpt - 1;
     return launch_step(c, 0, slot_ck(s), step_rho(s, -1), true);
   };
+  // single-wave workgroups on small grids, as the forward steps (whole call: 37 736
+  // cells 2 348 -> 2 316 us, 118 304 5 090 -> 4 965 us, with the anisotropic medium and FP64
+  // populations 6 820 -> 6 528 us)
+  const bool narrow = step_width(c, BLOCK) == 64;
   // the reverse step of step j of segment s; with `next` also the recording of the
   // next step of segment s - 1 (at time c->t)
   auto reverse_step = [&](int s, int j, bool next) -> lbm_status {
@@ -165,14 +169,23 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
     auto reverse = [&](auto an, auto ph_type, auto odd) {
       using PH = decltype(ph_type);
       constexpr bool AN = decltype(an)::value, OD = decltype(odd)::value;
+      const unsigned nw = (unsigned)blocks_for_nt(c->nc, 64);
       if (next)
         with_parity(c->t, [&](auto sodd) {
-          hipLaunchKernelGGL((k_adjoint_and_step<AN, PH, OD, decltype(sodd)::value>), dim3(2 * c->nblk), dim3(BLOCK),
-                             0, c->stream, c->P, ab, (uint32_t)n, ewn, okind, (uint32_t)c->nblk, b);
+          constexpr bool SO = decltype(sodd)::value;
+          if (narrow)
+            hipLaunchKernelGGL((k_adjoint_and_step<AN, PH, OD, SO, 64>), dim3(2 * nw), dim3(64), 0, c->stream, c->P, ab,
+                               (uint32_t)n, ewn, okind, nw, b);
+          else
+            hipLaunchKernelGGL((k_adjoint_and_step<AN, PH, OD, SO, BLOCK>), dim3(2 * c->nblk), dim3(BLOCK), 0, c->stream,
+                               c->P, ab, (uint32_t)n, ewn, okind, (uint32_t)c->nblk, b);
         });
+      else if (narrow)
+        hipLaunchKernelGGL((k_adjoint<AN, PH, OD, 64>), dim3(nw), dim3(64), 0, c->stream, c->P, ab, (uint32_t)n, ewn,
+                           okind);
       else
-        hipLaunchKernelGGL((k_adjoint<AN, PH, OD>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab, (uint32_t)n,
-                           ewn, okind);
+        hipLaunchKernelGGL((k_adjoint<AN, PH, OD, BLOCK>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, c->P, ab,
+                           (uint32_t)n, ewn, okind);
     };
     with_parity(n, [&](auto odd) {
       if (c->P.an_iters > 0 && p64) reverse(std::true_type{}, double{}, odd);

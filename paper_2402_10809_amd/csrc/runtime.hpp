@@ -177,6 +177,15 @@ inline unsigned dense_blocks(const lbm::Dense& out) {
 inline uint32_t diag_run(const lbm_ctx* c) { return (uint32_t)((c->nblk + DIAG_BLOCKS - 1) / DIAG_BLOCKS); }
 inline int diag_blocks(const lbm_ctx* c) { return (c->nblk + (int)diag_run(c) - 1) / (int)diag_run(c); }
 
+// Work-items per workgroup of a step: single waves on grids of less than four
+// workgroups of 256 per CU, where whole workgroups leave some CUs with one more
+// than others and a wave waits for its CU's memory pipe (FP32 step: 30 720 cells
+// 4.41 -> 4.31 us, 15 000 5.4 -> 4.95, 118 304 6.95 -> 6.83; D3Q27 at 142 000: BF16 9.38 ->
+// 8.78, FP32 10.6 -> 9.92). The line is where the two meet (231 000 cells: 9.05 and
+// 8.99 us); on 2.36 M cells single waves are 1 % slower.
+constexpr int NARROW_GRID = 1024;  // workgroups of 256 work-items
+inline int step_width(const lbm_ctx* c, int nt) { return c->nblk < NARROW_GRID ? 64 : nt; }
+
 // Storage dispatch for the per-storage launch functions.
 template <class Fn>
 void with_storage(int storage, Fn&& fn) {

@@ -1131,7 +1131,8 @@ __device__ __forceinline__ bool step_any(const Params& p, const Bufs& b, uint32_
 }
 
 // ---------------------------------------------------------------------------
-// The step at parity ODD (t odd), NT work-items per workgroup.  DIAG: 0 none,
+// The step at parity ODD (t odd), NT work-items per workgroup (fewer, in whole
+// waves, except with DIAG 1).  DIAG: 0 none,
 // 1 diagnostics of the pre-collision state into part[block][NDIAGP], 2 region
 // kinetic energy, 3 region wall shear stress |tau|, accumulated into
 // part[wave of 64 cells].  REC 1: also record the pulled values and omega_prev
@@ -1214,7 +1215,7 @@ template <class S, bool SHW, bool ODD, int DIAG, int REC, class R, bool PROJ, in
           bool WR = sizeof(S) == 4>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((ODD && sizeof(S) == 2 && DIAG == 0 && !REC) ? 5 : (sizeof(S) == 4 && DIAG == 0 && !REC && std::is_same<R, float>::value && !AN ? 4 : 1))))
 void k_step(Params p, Bufs b) {
-  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD) * NT + threadIdx.x;
+  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD) * (DIAG == 1 ? NT : blockDim.x) + threadIdx.x;
   step_body<S, SHW, ODD, DIAG, REC, R, PROJ, NT, AN, RM, WR>(p, b, c, blockIdx.x == 0);
 }
 

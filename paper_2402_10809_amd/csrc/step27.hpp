@@ -422,7 +422,7 @@ __device__ __forceinline__ void step_cell(const Params& p, const Bufs27& b, uint
 template <class S, bool SHW, bool ODD, int DIAG, class R, bool PROJ, int NT, int RM = 0>
 __global__ __launch_bounds__(NT) void k_step(Params p, Bufs27 b) {
   // backwards on odd steps with 16-bit storage: see step.hpp's k_step
-  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD && sizeof(S) == 2) * NT + threadIdx.x;
+  const uint32_t c = xcd_block(blockIdx.x, gridDim.x, ODD && sizeof(S) == 2) * (DIAG == 1 ? NT : blockDim.x) + threadIdx.x;
   const uint32_t t = b.tc[ODD ? 1 : 0];
   const uint64_t lk = c < (uint32_t)p.nc ? b.links[c] : L_DEAD;
   const bool active = !(lk & L_DEAD);
