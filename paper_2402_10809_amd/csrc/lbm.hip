@@ -1,6 +1,7 @@
 // Host runtime of liblbm.so: the C ABI declared in include/lbm.h.
 //
-// The library never allocates device memory: the caller's workspace is carved
+// The library never allocates device memory (a context keeps 88 bytes of pinned
+// host memory for the results of its reductions): the caller's workspace is carved
 // into the population buffer (one, streamed in place), the per-cell arrays of
 // the compact row layout (position code, link word, porosity, relaxation rate),
 // the per-row tables (neighbour-row deltas, inflow profile, box offset), plus
@@ -304,13 +305,14 @@ lbm_status launch_step(lbm_ctx* c, int diag, float* rec, float* rho_rec, bool fr
   return LBM_OK;
 }
 
-lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t ops, double* host_out,
-                    double* dev_out) {
-  double* dout = dev_out ? dev_out : (double*)(c->ws + c->L.diag);
-  launch_finalize(c->stream, part, nparts, n, ops, dout);
+// Reduce partials and wait for the result: the reduction writes it to the
+// context's pinned host memory itself (a copy behind it was a launch of 4 us and
+// as long again on the host: lbm_diagnostics on 2.36 M cells 71.1 -> 54.1 us).
+lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t ops, double* out) {
+  launch_finalize(c->stream, part, nparts, n, ops, c->host_out);
   HIP_TRY(c, hipGetLastError());
-  HIP_TRY(c, hipMemcpyAsync(host_out, dout, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  std::memcpy(out, c->host_out, n * sizeof(double));
   return LBM_OK;
 }
 
@@ -588,12 +590,13 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* solid, const float* p
              : (grid->arith == LBM_ARITH_AUTO && grid->storage == LBM_STORE_FP32) ? 1 : 0;
   c->omega0 = (float)(2.0 / (6.0 * rh->nu0 + 1.0));
 
-  auto bail = [&](lbm_status st) { delete c; return st; };
+  auto bail = [&](lbm_status st) { lbm_destroy(c); return st; };
 #define HIP_TRY0(expr)                                                                              \
   do {                                                                                              \
     hipError_t e_ = (expr);                                                                         \
     if (e_ != hipSuccess) return bail(fail(LBM_E_DEVICE, std::string(#expr) + ": " + hipGetErrorString(e_))); \
   } while (0)
+  HIP_TRY0(hipHostMalloc((void**)&c->host_out, NDIAGP * sizeof(double), hipHostMallocDefault));
   // slots that no consumer reads are never written by the kernels; clear them once
   HIP_TRY0(hipMemsetAsync(c->ws + c->L.A, 0, c->L.code - c->L.A, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.code, c->code.data(), c->code.size() * 4, hipMemcpyHostToDevice, c->stream));
@@ -693,7 +696,6 @@ lbm_status lbm_diagnostics(lbm_ctx* c, double* out) {
 lbm_status lbm_diagnostics_noalloc(lbm_ctx* c, double* out) {
   CTX_CHECK(c);
   if (!out) return fail(LBM_E_INVALID, "out is NULL");
-  const size_t part_bytes = align_up((size_t)c->nblk * NDIAGP * sizeof(double));
   const size_t need = noalloc_need(c->nblk);
   if (need > STATIC_SCRATCH_BYTES)
     return fail(LBM_E_INVALID, "lbm_diagnostics_noalloc needs " + std::to_string(need) +
@@ -704,11 +706,10 @@ lbm_status lbm_diagnostics_noalloc(lbm_ctx* c, double* out) {
   lbm_status s = scratch_address(c->device, &base);
   if (s != LBM_OK) return s;
   double* part = (double*)base;                      // every workgroup writes all its partials
-  double* dout = (double*)((char*)base + part_bytes);
   s = diag_launch(c, part);
   if (s != LBM_OK) return s;
   double dg[NDIAGP];
-  s = finalize(c, part, diag_blocks(c), NDIAGP, DIAG_OPS, dg, dout);
+  s = finalize(c, part, diag_blocks(c), NDIAGP, DIAG_OPS, dg);
   if (s != LBM_OK) return s;
   for (int k = 0; k < 10; ++k) out[k] = dg[k];
   out[10] = (double)c->t;
@@ -824,7 +825,10 @@ lbm_status lbm_bandwidth_probe(int kind, void* dst, const void* src, size_t byte
   return LBM_OK;
 }
 
-void lbm_destroy(lbm_ctx* c) { delete c; }
+void lbm_destroy(lbm_ctx* c) {
+  if (c && c->host_out) (void)hipHostFree(c->host_out);
+  delete c;
+}
 
 }  // extern "C"
 
