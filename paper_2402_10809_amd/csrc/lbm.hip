@@ -322,8 +322,9 @@ namespace {
 
 const uint32_t DIAG_OPS = (1u << 12) | (2u << 14) | (1u << 16);  // max |u|, min omega, max omega; rest sums
 
-// Fixed device scratch of lbm_diagnostics_noalloc: the per-block partials and
-// the reduced vector.  Each GPU the library runs on holds its own copy for the
+// Fixed device scratch of lbm_diagnostics_noalloc: the workgroups' partials (the
+// size limit counts a row per 256 cells and the reduced vector).  Each GPU the
+// library runs on holds its own copy for the
 // life of the process; host code reaches it only through the address that
 // hipGetSymbolAddress returns on that device (kept per device below).
 constexpr size_t STATIC_SCRATCH_BYTES = size_t(1) << 20;
