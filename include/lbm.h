@@ -45,6 +45,8 @@
  *   - The library never allocates device memory.  The caller supplies one
  *     device workspace of lbm_workspace_size() bytes (256-byte aligned) that
  *     must outlive the context, and owns every device output buffer.
+ *   - Pinned host memory: 8 KB per GPU, allocated by the first lbm_create there
+ *     and held until the process ends.
  *   - All device work is enqueued on the HIP stream given to lbm_create.
  *     Calls that return host data synchronise that stream.
  *   - A context is not thread-safe; distinct contexts are independent.
@@ -352,6 +354,8 @@ enum { LBM_PROBE_COPY = 0, LBM_PROBE_COPY_NT = 1, LBM_PROBE_READ = 2, LBM_PROBE_
 lbm_status lbm_bandwidth_probe(int kind, void* dst, const void* src, size_t bytes, void* stream);
 
 const char* lbm_last_error(void);
+/* Free the context (host memory only: no device call, so it neither waits for
+ * work on any stream nor disturbs a capture).  NULL is allowed. */
 void lbm_destroy(lbm_ctx* ctx);
 
 #ifdef __cplusplus

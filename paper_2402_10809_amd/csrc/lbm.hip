@@ -1,7 +1,7 @@
 // Host runtime of liblbm.so: the C ABI declared in include/lbm.h.
 //
-// The library never allocates device memory (a context keeps 88 bytes of pinned
-// host memory for the results of its reductions): the caller's workspace is carved
+// The library never allocates device memory (the results of its reductions go to
+// a few KB of pinned host memory, see HostSlots): the caller's workspace is carved
 // into the population buffer (one, streamed in place), the per-cell arrays of
 // the compact row layout (position code, link word, porosity, relaxation rate),
 // the per-row tables (neighbour-row deltas, inflow profile, box offset), plus
@@ -306,13 +306,16 @@ lbm_status launch_step(lbm_ctx* c, int diag, float* rec, float* rho_rec, bool fr
 }
 
 // Reduce partials and wait for the result: the reduction writes it to the
-// context's pinned host memory itself (a copy behind it was a launch of 4 us and
-// as long again on the host: lbm_diagnostics on 2.36 M cells 71.1 -> 54.1 us).
-lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t ops, double* out) {
-  launch_finalize(c->stream, part, nparts, n, ops, c->host_out);
+// context's slot of pinned host memory itself (a copy behind it was a launch of 4
+// us and as long again on the host: lbm_diagnostics on 2.36 M cells 71.1 -> 54.1
+// us).  A context without a slot copies it from dev_out.
+lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t ops, double* out, double* dev_out) {
+  if (!dev_out) dev_out = (double*)(c->ws + c->L.diag);
+  launch_finalize(c->stream, part, nparts, n, ops, c->host_out ? c->host_out : dev_out);
   HIP_TRY(c, hipGetLastError());
+  if (!c->host_out) HIP_TRY(c, hipMemcpyAsync(out, dev_out, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  std::memcpy(out, c->host_out, n * sizeof(double));
+  if (c->host_out) std::memcpy(out, c->host_out, n * sizeof(double));
   return LBM_OK;
 }
 
@@ -322,11 +325,12 @@ namespace {
 
 const uint32_t DIAG_OPS = (1u << 12) | (2u << 14) | (1u << 16);  // max |u|, min omega, max omega; rest sums
 
-// Fixed device scratch of lbm_diagnostics_noalloc: the workgroups' partials (the
-// size limit counts a row per 256 cells and the reduced vector).  Each GPU the
-// library runs on holds its own copy for the
-// life of the process; host code reaches it only through the address that
-// hipGetSymbolAddress returns on that device (kept per device below).
+// Fixed device scratch of lbm_diagnostics_noalloc: room for a row of partials per
+// 256 cells (of which k_diag's workgroups write the first), which sets the size
+// limit, and behind them the reduced vector of a context without a slot of pinned
+// memory.  Each GPU the library runs on holds its own copy for the life of the
+// process; host code reaches it only through the address that hipGetSymbolAddress
+// returns on that device (kept per device below).
 constexpr size_t STATIC_SCRATCH_BYTES = size_t(1) << 20;
 constexpr int MAX_DEVICES = 64;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
@@ -355,6 +359,50 @@ lbm_status scratch_address(int dev, void** out) {
   }
   *out = g_scratch_dev[dev];
   return LBM_OK;
+}
+
+// Pinned host memory for the results of reductions: one array of HOST_SLOTS slots
+// per GPU, allocated when the first context is created there and held until the
+// process ends; lbm_create takes a slot and lbm_destroy gives it back, which is
+// host work only.  (Memory of the context's own had to be freed with it: the
+// runtime's free waits for the work queued on every stream, and invalidates a
+// capture in progress on any.)  Contexts beyond HOST_SLOTS alive at once on a GPU
+// have none, and copy their results.
+constexpr int HOST_SLOTS = 64, HOST_SLOT_DOUBLES = 16;
+static_assert(NDIAGP <= HOST_SLOT_DOUBLES, "a slot holds the longest reduced vector");
+struct HostSlots {
+  double* at = nullptr;
+  uint64_t used = 0;  // one bit per slot
+};
+std::mutex g_slots_mu;
+HostSlots g_slots[MAX_DEVICES];
+
+// c->device is within range (scratch_address)
+void take_host_slot(lbm_ctx* c) {
+  std::lock_guard<std::mutex> lock(g_slots_mu);
+  HostSlots& h = g_slots[c->device];
+  if (!h.at) {
+    // allowed beside another thread's capture in this mode only
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    if (hipHostMalloc((void**)&h.at, HOST_SLOTS * HOST_SLOT_DOUBLES * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+      h.at = nullptr;
+      (void)hipGetLastError();
+    }
+    if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  if (!h.at || h.used == ~uint64_t(0)) return;
+  const int k = __builtin_ctzll(~h.used);
+  h.used |= uint64_t(1) << k;
+  c->host_out = h.at + k * HOST_SLOT_DOUBLES;
+}
+
+// A poisoned context may have left a reduction queued, so its slot is not used again.
+void give_host_slot(lbm_ctx* c) {
+  if (!c->host_out || c->poisoned) return;
+  std::lock_guard<std::mutex> lock(g_slots_mu);
+  HostSlots& h = g_slots[c->device];
+  h.used &= ~(uint64_t(1) << ((c->host_out - h.at) / HOST_SLOT_DOUBLES));
 }
 
 // nparts: the block count of the launch that wrote the partials
@@ -597,7 +645,7 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* solid, const float* p
     hipError_t e_ = (expr);                                                                         \
     if (e_ != hipSuccess) return bail(fail(LBM_E_DEVICE, std::string(#expr) + ": " + hipGetErrorString(e_))); \
   } while (0)
-  HIP_TRY0(hipHostMalloc((void**)&c->host_out, NDIAGP * sizeof(double), hipHostMallocDefault));
+  take_host_slot(c);
   // slots that no consumer reads are never written by the kernels; clear them once
   HIP_TRY0(hipMemsetAsync(c->ws + c->L.A, 0, c->L.code - c->L.A, c->stream));
   HIP_TRY0(hipMemcpyAsync(c->ws + c->L.code, c->code.data(), c->code.size() * 4, hipMemcpyHostToDevice, c->stream));
@@ -710,7 +758,8 @@ lbm_status lbm_diagnostics_noalloc(lbm_ctx* c, double* out) {
   s = diag_launch(c, part);
   if (s != LBM_OK) return s;
   double dg[NDIAGP];
-  s = finalize(c, part, diag_blocks(c), NDIAGP, DIAG_OPS, dg);
+  s = finalize(c, part, diag_blocks(c), NDIAGP, DIAG_OPS, dg,
+               (double*)((char*)base + align_up((size_t)c->nblk * NDIAGP * sizeof(double))));
   if (s != LBM_OK) return s;
   for (int k = 0; k < 10; ++k) out[k] = dg[k];
   out[10] = (double)c->t;
@@ -827,7 +876,7 @@ lbm_status lbm_bandwidth_probe(int kind, void* dst, const void* src, size_t byte
 }
 
 void lbm_destroy(lbm_ctx* c) {
-  if (c && c->host_out) (void)hipHostFree(c->host_out);
+  if (c) give_host_slot(c);
   delete c;
 }
 

@@ -80,7 +80,7 @@ struct lbm_ctx : lbmrt::HostLayout {
   bool poisoned = false;
   lbm::Params P{};
   float omega0 = 1.0f;
-  double* host_out = nullptr;     // pinned, mapped: where a reduction's result goes (finalize)
+  double* host_out = nullptr;     // slot of pinned, mapped memory for a reduction's result (null: none, see finalize)
   int amode = 1;                  // collision arithmetic: 0 FP32, 1 FP32 + projection, 2 FP64
 };
 
@@ -206,6 +206,8 @@ lbm_status launch_wave_info(lbm_ctx* c);
 lbm_status launch_init(lbm_ctx* c);
 // from: rec holds the record to step from (b.t = c->t) instead of receiving one
 lbm_status launch_step(lbm_ctx* c, int diag, float* rec, float* rho_rec, bool from = false);
-lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t ops, double* out);
+// dev_out: device area for the reduced vector of a context without a host slot (null: the workspace's)
+lbm_status finalize(lbm_ctx* c, const double* part, int nparts, int n, uint32_t ops, double* out,
+                    double* dev_out = nullptr);
 
 }  // namespace lbmrt
