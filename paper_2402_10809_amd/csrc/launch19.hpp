@@ -8,7 +8,7 @@ namespace lbmrt {
 template <class S>
 void step19(lbm_ctx* c, const lbm::Bufs& b, int diag, int rec) {
   constexpr int NT = std::is_same<S, float>::value ? 256 : STEP_NT16;
-  const int nt = diag == 1 ? NT : step_width(c, NT);
+  const int nt = diag == 1 ? NT : step_width(c, NT, std::is_same<S, float>::value && c->amode != 2 ? NARROW_FP32_D3Q19 : NARROW_GRID);
   const dim3 grid((unsigned)blocks_for_nt(c->nc, nt)), block((unsigned)nt);
   with_shift(c->grid.shift_mode, [&](auto shw) {
     constexpr bool SH = decltype(shw)::value;

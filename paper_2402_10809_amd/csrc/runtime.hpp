@@ -178,14 +178,22 @@ inline unsigned dense_blocks(const lbm::Dense& out) {
 inline uint32_t diag_run(const lbm_ctx* c) { return (uint32_t)((c->nblk + DIAG_BLOCKS - 1) / DIAG_BLOCKS); }
 inline int diag_blocks(const lbm_ctx* c) { return (c->nblk + (int)diag_run(c) - 1) / (int)diag_run(c); }
 
-// Work-items per workgroup of a step: single waves on grids of less than four
-// workgroups of 256 per CU, where whole workgroups leave some CUs with one more
-// than others and a wave waits for its CU's memory pipe (FP32 step: 30 720 cells
-// 4.41 -> 4.31 us, 15 000 5.4 -> 4.95, 118 304 6.95 -> 6.83; D3Q27 at 142 000: BF16 9.38 ->
-// 8.78, FP32 10.6 -> 9.92). The line is where the two meet (231 000 cells: 9.05 and
-// 8.99 us); on 2.36 M cells single waves are 1 % slower.
-constexpr int NARROW_GRID = 1024;  // workgroups of 256 work-items
-inline int step_width(const lbm_ctx* c, int nt) { return c->nblk < NARROW_GRID ? 64 : nt; }
+// Work-items per workgroup of a step: single waves on grids of less than `line`
+// workgroups of 256, where whole workgroups leave some CUs with one more than others
+// and a wave waits for its CU's memory pipe.  At most three (FP32 D3Q19 step) or four
+// (the others) workgroups per CU, from both widths at 16 to 1 300 workgroups (boxes,
+// channels, vessels; whole -> single waves, us per step):
+//   FP32 D3Q19: 272 workgroups 6.05 -> 5.82, 733 8.60 -> 8.50, 760 8.20 -> 8.28; above three
+//     per CU 880 9.15 -> 8.80, but 781 8.8 -> 9.4, 800 8.6 -> 9.0, 992 9.1 -> 9.4, 1 020 8.8 -> 9.3;
+//   16-bit D3Q19: 528 6.39 -> 6.09, 720 6.71 -> 6.55, 981 7.98 -> 7.88, 1 040 8.16 -> 8.22;
+//   D3Q27, FP32 and BF16: 528 9.01 -> 8.85 and 7.44 -> 7.22, 900 11.11 -> 11.21 and 9.23 ->
+//     9.18, 989 11.61 -> 11.34 and 10.28 -> 10.13, 1 020 11.50 -> 11.57 and 9.29 -> 9.35;
+//   a gradient of 40 steps (FP32; anisotropic, FP64 populations): 285 977 -> 920 and
+//     1 197 -> 1 134, 911 1 631 -> 1 616 and 2 215 -> 2 167.
+// Where the workgroups come out even (just below a multiple of 256) the two are
+// equal or single waves up to 2 % slower; on 2.36 M cells they are 1 % slower.
+constexpr int NARROW_FP32_D3Q19 = 768, NARROW_GRID = 1024;
+inline int step_width(const lbm_ctx* c, int nt, int line = NARROW_GRID) { return c->nblk < line ? 64 : nt; }
 
 // Storage dispatch for the per-storage launch functions.
 template <class Fn>
