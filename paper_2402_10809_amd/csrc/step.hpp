@@ -1162,11 +1162,19 @@ __device__ __forceinline__ bool step_any(const Params& p, const Bufs& b, uint32_
 // One workgroup's part of the step: cell c, first: the workgroup that sets the time.
 template <class S, bool SHW, bool ODD, int DIAG, int REC, class R, bool PROJ, int NT, bool AN, int RM, bool WR>
 __device__ __forceinline__ void step_body(const Params& p, const Bufs& b, uint32_t c, bool first) {
-  const uint32_t t = REC == 2 ? b.t : b.tc[ODD ? 1 : 0];
+  uint32_t t = REC == 2 ? b.t : b.tc[ODD ? 1 : 0];
   double dv[NDIAGP];
   float ke_reg = 0.0f;
   if constexpr (DIAG == 0 && WR) {
-    const WaveInfo wi = b.winfo[__builtin_amdgcn_readfirstlane(c >> 6)];
+    WaveInfo wi = b.winfo[__builtin_amdgcn_readfirstlane(c >> 6)];
+    // even steps: one wait for the record, the time and the populations' address; left
+    // to itself the compiler loads the latter two behind the branches on the record,
+    // a second scalar latency in front of a wave's loads (FP32, mean of both parities:
+    // 6.78 -> 6.70 us on 118 304 cells, 8.48 -> 8.26 on 187 576).  Odd steps spill more
+    // scalars with it (66 instead of 40) and take 0.9 % longer on the 9.4 M-cell box;
+    // the joint launches of a gradient take 1-3 % longer.
+    if constexpr (REC == 0 && !ODD && std::is_same<R, float>::value)
+      asm volatile("" : "+s"(wi.flags), "+s"(t) : "s"(b.A));
     if (wi.flags & WV_FLUID) {
       const bool uni = (wi.flags & WV_UNI) != 0, inr = (wi.flags & WV_INR) != 0;
       if (uni ? (!ODD || inr) : inr) {
