@@ -706,15 +706,20 @@ lbm_status lbm_moments(lbm_ctx* c, float* rho, float* u, float* shear, float* om
   d.lines = (const int2*)(c->ws + c->L.lines);
   d.nbox = (uint32_t)c->nbox;
   d.vec = c->P.nx % 4 == 0;
+  d.xcd = !c->beyond_cache;
   size_t bytes = 0;
+  int nplane = 0;
   for (const float* o : d.o) {
     if (!o) continue;
+    nplane += 1;
     bytes += c->nbox * 4;
     d.vec = d.vec && ((uintptr_t)o & 15) == 0;
   }
   if ((size_t)c->nc < c->nbox) {  // else the rows cover the box
-    // the zeros outside the rows: see k_moments
-    d.rest = bytes <= DENSE_CACHED;
+    // the zeros outside the rows, in the same launch or as clears first: see k_moments
+    const int clears = (rho != nullptr) + (u != nullptr) + (shear != nullptr) + (omega != nullptr) + (sigma != nullptr) +
+                       (tau != nullptr);
+    d.rest = bytes <= DENSE_CACHED && (d.vec ? nplane >= 2 : clears >= 3);
     if (!d.rest) {
       const size_t nb = c->nbox * 4;
       if (rho) HIP_TRY(c, hipMemsetAsync(rho, 0, nb, c->stream));

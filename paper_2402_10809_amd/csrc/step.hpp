@@ -1237,6 +1237,7 @@ struct Dense {
   uint32_t nbox;         // voxels
   int rest;              // whether this launch writes the zeros outside the rows
   int vec;               // four voxels at a time there: nx % 4 == 0 and every plane on 16 bytes
+  int xcd;               // whether each XCD takes one contiguous share of the rows
 };
 constexpr uint32_t DENSE_REST = 16 * BLOCK;  // voxels per workgroup of that part
 
@@ -1302,12 +1303,18 @@ __device__ __forceinline__ void dense_dead(const Dense& out, size_t idx) {
 // of every plane is written once in one launch.
 // That is for outputs that fit the Infinity Cache (DENSE_CACHED bytes, the
 // launch in lbm_moments), where clearing the planes first costs a launch of 3 to
-// 12 us each: rho, u, shear, omega, tau of 192x128x128 (113 MB) 37 -> 20 us, of
-// 203x131x117 (112 MB, odd sizes, D3Q27) 43 -> 19 us, rho, u, shear, omega of
-// 32^3 11 -> 4.5 us.  Beyond it the writes to memory bound it (512x320x320, 1.9 GB:
-// one launch 397 us, clears and cells 286 + 103 us; the zeros plane by plane in
-// the same launch, in 64 KB chunks 466 us, in one moving window 428 us), and the
-// planes are cleared first.
+// 12 us each: rho, u, shear, omega, tau of 192x128x128 (113 MB) 43 -> 29 us a call, of
+// 203x131x131 (125 MB, odd sizes) 52 -> 31, rho, u, shear, omega of 32^3 11 -> 4.5 us.
+// Beyond it the writes to memory bound it and the planes are cleared first (one
+// launch against clears: 301 MB 75 and 77 us, 332 MB 91 and 86, 498 MB 124.5 and 119.8,
+// 746 MB 186 and 168; 512x320x320, 1.9 GB, 397 and 389).  So they are where there is
+// little to save: one plane (25 MB 22.6 and 22.0 us, 210 MB 104 and 91), and with less
+// than three buffers to clear where the zeros go one voxel at a time (390x260x260:
+// one plane 67 and 41 us, two 72 and 60; 261x176x176: rho and u 39.3 and 38.4, with shear
+// and omega 45 and 52).
+// The rows in XCD shares (out.xcd) find what the last step left in each L2; a state
+// beyond the Infinity Cache streams faster in launch order (754 520 cells: 34.4 and
+// 36.4 us; 3.84 M cells, rho: 79.3 and 74.1, five planes 106 and 101).
 template <class S, bool SHW, bool ODD, class R, bool AN>
 __global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs b, uint32_t t, uint32_t nblk, Dense out) {
   if (blockIdx.x >= nblk) {
@@ -1315,7 +1322,7 @@ __global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs b, uint32_t t,
     else dense_rest<1>(p, out, blockIdx.x - nblk);
     return;
   }
-  const uint32_t c = xcd_block(blockIdx.x, nblk) * BLOCK + threadIdx.x;
+  const uint32_t c = (out.xcd ? xcd_block(blockIdx.x, nblk) : blockIdx.x) * BLOCK + threadIdx.x;
   if (c >= (uint32_t)p.nc) return;
   const uint32_t lk = b.links[c];
   Pos q = position(p, c, b.code[c]);

@@ -453,7 +453,7 @@ __global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs27 b, uint32_t 
     else dense_rest<1>(p, out, blockIdx.x - nblk);
     return;
   }
-  const uint32_t c = xcd_block(blockIdx.x, nblk) * BLOCK + threadIdx.x;
+  const uint32_t c = (out.xcd ? xcd_block(blockIdx.x, nblk) : blockIdx.x) * BLOCK + threadIdx.x;
   if (c >= (uint32_t)p.nc) return;
   const uint64_t lk = b.links[c];
   Pos q = position(p, c, b.code[c]);
