@@ -278,8 +278,9 @@ lbm_status lbm_diagnostics_noalloc(lbm_ctx* ctx, double* out);
  * populations (unshifted, FP64), omega[n_fluid] the relaxation rate of the
  * previous step.  Populations that would arrive through an open face are
  * unknown: get writes 0 there, set ignores them; the extrapolation outflow's
- * are part of the state instead (get returns them, set uses them).  Both sync
- * the stream. */
+ * are part of the state instead (get returns them, set uses them).  Values that
+ * are not finite (a diverged run) are returned as they are.  Both sync the
+ * stream. */
 lbm_status lbm_get_state(lbm_ctx* ctx, double* f, float* omega);
 lbm_status lbm_set_state(lbm_ctx* ctx, const double* f, const float* omega);
 

@@ -1412,8 +1412,8 @@ __device__ __forceinline__ double rest_value(double w, float phi) {
 // exactly as the stored values convert: v / U plus the rest value, the product
 // and the sum rounded each (no contraction).  Open-face unknowns are 0, except
 // the extrapolation outflow's, which are part of the state: their value at time
-// t is extrapolated as the next step would.  omega (null: not asked for) is the
-// relaxation rate in fluid order.
+// t is extrapolated as the next step would.  A value that is not a number stays
+// one.  omega (null: not asked for) is the relaxation rate in fluid order.
 template <class S, bool SHW, bool ODD>
 __global__ __launch_bounds__(BLOCK) void k_state_out(Params p, Bufs b, const uint32_t* wrank, double* out, float* omega,
                                                      int i0, int i1, uint32_t nf) {
@@ -1439,7 +1439,7 @@ __global__ __launch_bounds__(BLOCK) void k_state_out(Params p, Bufs b, const uin
   sfor<0, Q>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
     if (I < i0 || I >= i1) return;
-    const bool none = (open_unknown<I>(lk) && !kept_unknown<I>(p, lk)) || __builtin_isnan(d[I]);
+    const bool none = open_unknown<I>(lk) && !kept_unknown<I>(p, lk);
     const double v = (double)d[I] * p.d.iU;
     const double f = v + rest_value<SHW>(I == 0 ? 1.0 / 3.0 : (I < 7 ? 1.0 / 18.0 : 1.0 / 36.0), phi);
     out[(size_t)(I - i0) * nf + k] = none ? 0.0 : f;

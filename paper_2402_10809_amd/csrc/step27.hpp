@@ -551,7 +551,7 @@ __global__ __launch_bounds__(BLOCK) void k_state_out(Params p, Bufs27 b, const u
   sfor<0, Q>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
     if (I < i0 || I >= i1) return;
-    const bool none = (open_unknown<I>(lk) && !kept_unknown<I>(p, lk)) || __builtin_isnan(d[I]);
+    const bool none = open_unknown<I>(lk) && !kept_unknown<I>(p, lk);
     const double v = (double)d[I] * p.d.iU;
     const double f = v + rest_value<SHW>(kw(I) / 216.0, phi);
     out[(size_t)(I - i0) * nf + k] = none ? 0.0 : f;
