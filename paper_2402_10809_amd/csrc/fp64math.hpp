@@ -21,13 +21,9 @@ __host__ __device__ inline double ln_pos(double x) {
     m *= 2.0;
     k -= 1;
   }
-  // s = (m - 1) / (m + 1): the hardware (device) or FP32 (host) reciprocal refined by two Newton steps
+  // s = (m - 1) / (m + 1): FP32 reciprocal refined by two Newton steps
   const double den = m + 1.0;
-#ifdef __HIP_DEVICE_COMPILE__
-  double r = __builtin_amdgcn_rcp(den);
-#else
   double r = (double)(1.0f / (float)den);
-#endif
   r = r * (2.0 - den * r);
   r = r * (2.0 - den * r);
   const double s = (m - 1.0) * r;
