@@ -56,7 +56,7 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
   double* omh = (double*)(c->ws + L.omh);
   double* phih = (double*)(c->ws + L.phih);
   double* objp = (double*)(c->ws + L.obj);
-  const int nseg = (T + ckpt - 1) / ckpt, s_last = nseg - 1, t0_last = s_last * ckpt;
+  const int nseg = (int)(((int64_t)T + ckpt - 1) / ckpt), s_last = nseg - 1, t0_last = s_last * ckpt;
   // On grids that leave the chip idle a reverse or a recompute step is bound by
   // the latency of its waves, so one launch takes a step of each: while segment s
   // is reversed, segment s - 1 is recomputed. On larger grids both are bound by
@@ -68,9 +68,10 @@ extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, i
   // segment s; the density of the step before a segment has a place of its own.
   std::vector<int> free_slots, held[2];
   if (want_grad) {
-    for (int k = ckpt; k >= 0; --k) free_slots.push_back(k);
-    held[0].assign(ckpt, 0);
-    held[1].assign(ckpt, 0);
+    const int steps = std::min(ckpt, T);  // of a segment
+    for (int k = steps; k >= 0; --k) free_slots.push_back(k);
+    held[0].assign(steps, 0);
+    held[1].assign(steps, 0);
   }
   auto take_slot = [&](int s, int j) {
     held[s & 1][j] = free_slots.back();

@@ -138,11 +138,11 @@ Layout make_layout(const lbm_grid& g, int64_t nc, int64_t nrow, int T, int ckpt)
   L.T = T;
   L.ckpt = ckpt;
   if (T > 0) {
-    L.nck = (T + ckpt - 1) / ckpt;
+    L.nck = (int)(((int64_t)T + ckpt - 1) / ckpt);
     L.ck = take((size_t)L.nck * (Q + 1) * plane_cells(nc) * 4);
     // a segment's steps and one more; the densities also of the steps before two segments
-    L.rec = take((size_t)(ckpt + 1) * (Q + 1) * plane_cells(nc) * 4);
-    L.rho = take((size_t)(ckpt + 3) * plane_cells(nc) * 4);
+    L.rec = take(((size_t)ckpt + 1) * (Q + 1) * plane_cells(nc) * 4);
+    L.rho = take(((size_t)ckpt + 3) * plane_cells(nc) * 4);
     L.ah = take(Q * (size_t)plane_cells(nc) * 8);  // adjoint populations, in place: room for FP64
     L.omh = take((size_t)nc * 8);
     L.phih = take((size_t)nc * 8);
