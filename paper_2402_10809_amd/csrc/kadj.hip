@@ -17,7 +17,10 @@ using namespace lbmrt;
 // state follow the parity of its time.  The forward pass records the last segment
 // itself (that segment needs no checkpoint and no recompute); with one segment
 // (ckpt_every >= T) nothing is recomputed.  The recompute reproduces the forward
-// trajectory bit for bit, so the records are the same either way.
+// trajectory bit for bit, so the records are the same either way.  That the forms of
+// the step the two take (with an objective or not, through the wave records or the
+// link words, alone or joint, 64 or 256 work-items) round alike is the compiler's
+// doing; the tests compare segment lengths on lattices that reach all of them.
 extern "C" lbm_status lbm_adjoint(lbm_ctx* c, const lbm_objective* obj, int T, int ckpt, double* J,
                                   float* dJ_dphi) {
   CTX_CHECK(c);
