@@ -54,11 +54,11 @@ B_ALG_ADJ = 256 + 168
 # what this implementation moves per cell and time step: forward pass 164,
 # recompute with the record written (164 + 19 pulled values + omega_prev + rho
 # = 248), reverse step (record 80, adjoint populations 152, porosity 4,
-# neighbour rho 4, omega adjoint 8, FP64 porosity adjoint 16 = 264)
-B_IMPL_ADJ = 164 + 248 + 264
+# neighbour rho 4, FP64 omega adjoint 16, FP64 porosity adjoint 16 = 272)
+B_IMPL_ADJ = 164 + 248 + 272
 # with one segment (ckpt_every = T: the whole record resident in HBM) the
-# forward pass writes the record and nothing is recomputed: 248 + 264
-B_IMPL_ADJ_1SEG = 248 + 264
+# forward pass writes the record and nothing is recomputed: 248 + 272
+B_IMPL_ADJ_1SEG = 248 + 272
 
 
 def log(msg):

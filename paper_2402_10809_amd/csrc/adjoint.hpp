@@ -632,7 +632,10 @@ void k_adjoint(Params p, AdjBufs a, uint32_t t, float ew, int kind) {
 // The reverse step of n and a recording step (parity SODD) of the segment before
 // it in one launch, the first nblk workgroups and the others: neither depends on
 // the other.  For grids that leave the chip idle, where either step is bound by
-// the latency of its waves (launch in lbm_adjoint).
+// the latency of its waves (launch in lbm_adjoint).  With both bodies in one kernel
+// most anisotropic forms and one or two of the others need 36 bytes of scratch per
+// work-item for scalars beyond the vector lanes that hold spilled ones; k_adjoint
+// needs none.
 template <bool AN, class PH, bool ODD, bool SODD, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(adjoint_waves<AN, PH>())))
 void k_adjoint_and_step(Params p, AdjBufs a, uint32_t t, float ew, int kind, uint32_t nblk, Bufs b) {

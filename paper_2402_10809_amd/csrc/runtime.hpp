@@ -29,8 +29,8 @@ inline int qof(const lbm_grid& g) { return g.velocity_set == 27 ? 27 : 19; }
 inline int blocks_for(int64_t n) { return (int)((n + BLOCK - 1) / BLOCK); }
 inline int blocks_for_nt(int64_t n, int nt) { return (int)((n + nt - 1) / nt); }
 
-// Workgroup size of the step kernel: 256 work-items with FP32 storage, 64 with
-// the 16-bit forms (measured fastest for each on the large aneurysm).
+// Work-items per workgroup of the step kernel: 256 on large grids, single waves on
+// small ones (step_width).
 constexpr int STEP_NT_MIN = 64;
 constexpr int MAX_WAVE_TABLE = 1024;  // samples of a sampled inflow waveform
 constexpr int STEP_NT16 = 256;  // work-items per workgroup of the 16-bit step kernels
@@ -44,7 +44,9 @@ inline int step_nt(int storage) { return storage == LBM_STORE_FP32 ? 256 : STEP_
 // 5 061 us (checkpoints every 16 or 20 steps); 296 748 5 986 -> 5 500 us, 538 068
 // 9 089 -> 8 538 us, 823 756 12 786 -> 12 187 us, 1 308 792 18 728 -> 18 643 us (with the
 // anisotropic medium and FP64 populations 19 396 -> 19 037 and 28 665 -> 32 568 us
-// for the last two), 2 360 212 27 023 -> 31 349 us.
+// for the last two), 2 360 212 27 023 -> 31 349 us.  One line for the four forms, just
+// below the largest size at which each of those measured gains; alone, the isotropic
+// FP32 form breaks even at about 1.3 M cells, the anisotropic FP64 form loses there.
 constexpr int64_t TOGETHER_CELLS = 786432;
 
 struct Layout {
