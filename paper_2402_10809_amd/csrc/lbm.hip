@@ -276,8 +276,8 @@ lbm_status launch_init(lbm_ctx* c) {
   // extrapolation outflow: the kept values of the rest state (phi = 1 on the
   // outflow cells, so w_i, i.e. deviation 0; the -x neighbour's values are
   // those the rest state's outflow populations extrapolate from)
-  HIP_TRY(c, hipMemsetAsync(c->ws + c->L.side, 0, (size_t)2 * c->nrow * (c->q == 27 ? 18 : 10) * sizeof(float),
-                            c->stream));
+  launch_zero(c->stream, (float*)(c->ws + c->L.side), (size_t)2 * c->nrow * (c->q == 27 ? 18 : 10));
+  HIP_TRY(c, hipGetLastError());
   c->t = 0;
   return LBM_OK;
 }
@@ -721,13 +721,13 @@ lbm_status lbm_moments(lbm_ctx* c, float* rho, float* u, float* shear, float* om
                        (tau != nullptr);
     d.rest = bytes <= DENSE_CACHED && (d.vec ? nplane >= 2 : clears >= 3);
     if (!d.rest) {
-      const size_t nb = c->nbox * 4;
-      if (rho) HIP_TRY(c, hipMemsetAsync(rho, 0, nb, c->stream));
-      if (u) HIP_TRY(c, hipMemsetAsync(u, 0, 3 * nb, c->stream));
-      if (shear) HIP_TRY(c, hipMemsetAsync(shear, 0, nb, c->stream));
-      if (omega) HIP_TRY(c, hipMemsetAsync(omega, 0, nb, c->stream));
-      if (sigma) HIP_TRY(c, hipMemsetAsync(sigma, 0, 6 * nb, c->stream));
-      if (tau) HIP_TRY(c, hipMemsetAsync(tau, 0, 3 * nb, c->stream));
+      if (rho) launch_zero(c->stream, rho, c->nbox);
+      if (u) launch_zero(c->stream, u, 3 * c->nbox);
+      if (shear) launch_zero(c->stream, shear, c->nbox);
+      if (omega) launch_zero(c->stream, omega, c->nbox);
+      if (sigma) launch_zero(c->stream, sigma, 6 * c->nbox);
+      if (tau) launch_zero(c->stream, tau, 3 * c->nbox);
+      HIP_TRY(c, hipGetLastError());
     }
   }
   return moments_launch(c, d);

@@ -207,6 +207,9 @@ void with_storage(int storage, Fn&& fn) {
 
 // Kernels without a storage type (kmisc.hip).
 void launch_finalize(hipStream_t s, const double* part, int nparts, int n, uint32_t ops, double* out);
+// n > 0 floats to zero, by a kernel, so that the calls that clear can be captured: memsets
+// recorded into a graph left wrong values on its replays.
+void launch_zero(hipStream_t s, float* p, size_t n);
 void launch_copy(hipStream_t s, const void* src, void* dst, size_t n16, unsigned blocks);
 void launch_probe(hipStream_t s, int kind, const void* src, void* dst, size_t n16, unsigned blocks);
 lbm_status set_porosity_device(lbm_ctx* c, const float* phib, uint32_t* bad_cell);
