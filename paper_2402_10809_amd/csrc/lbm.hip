@@ -591,7 +591,8 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* solid, const float* p
   c->nblk = blocks_for(c->nc);
   c->sblk = blocks_for_nt(c->nc, step_nt(grid->storage));
   // populations, position code, link word, porosity and relaxation rate
-  c->beyond_cache = (size_t)c->nc * ((size_t)c->q * store_bytes(grid->storage) + 16) > INFINITY_CACHE_BYTES;
+  c->state_bytes = (size_t)c->nc * ((size_t)c->q * store_bytes(grid->storage) + 16);
+  c->beyond_cache = c->state_bytes > INFINITY_CACHE_BYTES;
   c->L = L0;
   c->ws = (char*)workspace;
   c->ws_bytes = ws_bytes;
@@ -706,7 +707,8 @@ lbm_status lbm_moments(lbm_ctx* c, float* rho, float* u, float* shear, float* om
   d.lines = (const int2*)(c->ws + c->L.lines);
   d.nbox = (uint32_t)c->nbox;
   d.vec = c->P.nx % 4 == 0;
-  d.xcd = !c->beyond_cache;
+  // see k_moments
+  d.xcd = c->q == 19 || c->grid.storage != LBM_STORE_FP32 || c->state_bytes <= INFINITY_CACHE_BYTES / 8 * 9;
   size_t bytes = 0;
   int nplane = 0;
   for (const float* o : d.o) {
@@ -716,10 +718,8 @@ lbm_status lbm_moments(lbm_ctx* c, float* rho, float* u, float* shear, float* om
     d.vec = d.vec && ((uintptr_t)o & 15) == 0;
   }
   if ((size_t)c->nc < c->nbox) {  // else the rows cover the box
-    // the zeros outside the rows, in the same launch or as clears first: see k_moments
-    const int clears = (rho != nullptr) + (u != nullptr) + (shear != nullptr) + (omega != nullptr) + (sigma != nullptr) +
-                       (tau != nullptr);
-    d.rest = bytes <= DENSE_CACHED && (d.vec ? nplane >= 2 : clears >= 3);
+    // the zeros outside the rows, in the same launch or as clears first
+    d.rest = bytes <= DENSE_CACHED && (d.vec || nplane >= 4);
     if (!d.rest) {
       if (rho) launch_zero(c->stream, rho, c->nbox);
       if (u) launch_zero(c->stream, u, 3 * c->nbox);

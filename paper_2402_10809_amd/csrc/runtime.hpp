@@ -69,7 +69,8 @@ struct lbm_ctx : lbmrt::HostLayout {
   size_t nbox = 0;
   int nblk = 0;                   // blocks of BLOCK work-items over the compact cells
   int sblk = 0;                   // blocks of the step kernel
-  bool beyond_cache = false;      // the step's state (populations + per-cell arrays) exceeds the Infinity Cache
+  size_t state_bytes = 0;         // the step's state: populations and per-cell arrays
+  bool beyond_cache = false;      // it exceeds the Infinity Cache
   int64_t nwss = 0;               // region cells on the wall (with a wall normal)
   int q = 19;                     // velocity set
   double U = 36.0;

@@ -1303,18 +1303,21 @@ __device__ __forceinline__ void dense_dead(const Dense& out, size_t idx) {
 // of every plane is written once in one launch.
 // That is for outputs that fit the Infinity Cache (DENSE_CACHED bytes, the
 // launch in lbm_moments), where clearing the planes first costs a launch of 3 to
-// 12 us each: rho, u, shear, omega, tau of 192x128x128 (113 MB) 43 -> 29 us a call, of
-// 203x131x131 (125 MB, odd sizes) 52 -> 31, rho, u, shear, omega of 32^3 11 -> 4.5 us.
-// Beyond it the writes to memory bound it and the planes are cleared first (one
-// launch against clears: 301 MB 75 and 77 us, 332 MB 91 and 86, 498 MB 124.5 and 119.8,
-// 746 MB 186 and 168; 512x320x320, 1.9 GB, 397 and 389).  So they are where there is
-// little to save: one plane (25 MB 22.6 and 22.0 us, 210 MB 104 and 91), and with less
-// than three buffers to clear where the zeros go one voxel at a time (390x260x260:
-// one plane 67 and 41 us, two 72 and 60; 261x176x176: rho and u 39.3 and 38.4, with shear
-// and omega 45 and 52).
-// The rows in XCD shares (out.xcd) find what the last step left in each L2; a state
-// beyond the Infinity Cache streams faster in launch order (754 520 cells: 34.4 and
-// 36.4 us; 3.84 M cells, rho: 79.3 and 74.1, five planes 106 and 101).
+// 12 us each and displaces the state that the steps before left in the cache: rho, u,
+// shear, omega of 192x128x128 (75 MB) 18 -> 12 us after four steps, rho of 512x320x320 (210
+// MB) 50 -> 36, of 32^3 11 -> 4.5 with the other three.  With larger outputs the writes to memory
+// take over and the two come out mixed (after four steps, clears and one launch: rho, u of
+// 360x240x240, 332 MB, 67 and 53 us, all planes, 1.2 GB, 250 and 263; all planes of
+// 304x203x203, 752 MB, 155 and 163, of 305x203x203 155 and 205): those are cleared first.
+// Where the zeros go one voxel at a time (nx % 4 or an unaligned plane) the address
+// work must be shared by four planes at least: 261x176x176 rho 13 us with clears, 22 in one
+// launch, omega and rho 19 and 22, rho and u 27 and 24; 390x260x260 rho 28 and 52.
+// The rows go in XCD shares (out.xcd): the last step's lines are in the L2 of the XCD
+// that meets them again, and its last cells in the Infinity Cache (after two steps, in
+// shares and in launch order: 2.29 M cells, 201 MB, five planes 60 and 71 us; 3.28 M cells,
+// 288 MB, 75 and 89).  The D3Q27 FP32 step, which keeps one direction, leaves its first
+// cells displaced once the state exceeds the cache: launch order from there (279 MB 122
+// and 122 us, 310 MB 88 and 73).
 template <class S, bool SHW, bool ODD, class R, bool AN>
 __global__ __launch_bounds__(BLOCK) void k_moments(Params p, Bufs b, uint32_t t, uint32_t nblk, Dense out) {
   if (blockIdx.x >= nblk) {
